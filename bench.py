@@ -99,6 +99,8 @@ def algorithmic_bytes(rec, f=4, fi=4, maxit=PCG_ITERS):
         if tag >= maxit:       # last update x += a p
             return 3 * f * n
         return 10 * f * n      # reads x, r, p, w, diag, off; writes x, r, p, w
+    if k == "pcg_solve":       # a whole solve in one launch: reads rhs, diag, off; writes x
+        return 4 * f * n
     if k == "loss_grad":       # reads I+, I-, b (and q); writes grad, diag, off (and b + g q)
         return 2 * fi * c + (6 if tag else 4) * f * n
     if k == "trial":           # reads I+, I-, b, q
@@ -135,6 +137,7 @@ def table_rule_bytes(rec, f=4, fi=4):
 
 BYTES_RULE = {
     "pcg_step": "full iteration: reads x,r,p,w,diag,off, writes x,r,p,w (40 B/node)",
+    "pcg_solve": "whole solve: reads rhs,diag,off, writes x (16 B/node); the vectors stay on the chip",
     "loss_grad": "reads I+,I-,b[,q], writes grad,diag,off[,b+gq] (8 B/cell + 16 or 24 B/node)",
     "trial": "reads I+,I-,b,q (8 B/cell + 8 B/node)",
     "hvp": "reads v,diag,off, writes Hv (16 B/node)",
@@ -241,7 +244,18 @@ def pmc_probe():
     Im = torch.as_tensor(pair.I_minus).to(dev, torch.float32).contiguous()
     b = torch.zeros(rgp.field_shape(pair.shape, pair.pe), dtype=torch.float32, device=dev)
     _, g, hd, ho = rgp.loss_grad(Ip, Im, b, pair.pe)
-    x, its, rel = rgp.pcg_solve(hd, ho, -g, pair.shape, pair.pe, maxit=PCG_ITERS, rtol=0.0)
+    # the stepped form (k_pcg_step), which a captured call takes
+    rhs, ws = -g, torch.zeros(rgp.workspace_size(rgp.OP_PCG_SOLVE, pair.shape, pair.pe, (1, 1, 1),
+                                                 torch.float32), dtype=torch.uint8, device=dev)
+    x = torch.empty_like(rhs)
+    its = torch.zeros(1, dtype=torch.int32, device=dev)
+    rel = torch.zeros(1, dtype=torch.float64, device=dev)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rgp.pcg_solve_into(hd, ho, rhs, x, pair.shape, pair.pe, PCG_ITERS, ws, iters=its, relres=rel,
+                           stream=torch.cuda.current_stream())
+    graph.replay()
     torch.cuda.synchronize()
     log(f"pmc probe: PCG {int(its.item())} iterations, relres {float(rel.item()):.3e}")
 
@@ -627,7 +641,7 @@ def batch_bench(pairs, steps, scale):
     batch_long.close()
     kernels = {}
     for name, rec in summarize_records(recs).items():
-        if rec["kernel"] not in ("pcg_step", "loss_grad", "trial"):
+        if rec["kernel"] not in ("pcg_step", "pcg_solve", "loss_grad", "trial"):
             continue
         if rec["cells"] < sum(int(np.prod(sh)) for sh in shapes) // 80:
             continue   # a single pair's launch (the batch shares only the Gauss-Newton kernels)
@@ -926,9 +940,11 @@ def size_sweep(steps):
         rgp.correct_into(Ip, Im, pe, opts, b, Tp, Tm, ws, stream=side)
         torch.cuda.synchronize()
         recs = rgp.timing_stop(1 << 14)
-        nb = max(r["nodes"] for r in recs if r["kernel"] == "pcg_step")
+        nb = max(r["nodes"] for r in recs if r["kernel"] in ("pcg_step", "pcg_solve"))
         full = [r["ms"] * 1e3 for r in recs if r["kernel"] == "pcg_step" and r["nodes"] == nb
                 and 0 < r["tag"] < PCG_ITERS]
+        full += [r["ms"] * 1e3 / r["tag"] for r in recs
+                 if r["kernel"] == "pcg_solve" and r["nodes"] == nb]
         us = statistics.median(full)
         gbps = 40.0 * nb / (us * 1e3)
         row = dict(shape=list(shape), nodes=int(nb), ms_per_pair=round(1e3 * wall, 3),
@@ -1164,18 +1180,25 @@ def main():
                                          for c in copy))
 
     nb = int(np.prod(rgp.field_shape(shape, pe)))
-    dom = next(r for r in kernels.values() if r["kernel"] == "pcg_step" and r["nodes"] == nb)
-    traffic = measured_traffic()
-    # achieved: the measurement table's per-unit figure for a PCG iteration (52 B per cell)
-    # over the measured mean launch; moved_bytes: what this fused kernel must move (40 B/node)
+    dom = next(r for r in kernels.values()
+               if r["kernel"] in ("pcg_solve", "pcg_step") and r["nodes"] == nb)
+    # a solve in one launch: its iterations share the launch
+    iters = PCG_ITERS if dom["kernel"] == "pcg_solve" else 1
+    dom = dict(dom, us_mean=dom["us_mean"] / iters, us_median=dom["us_median"] / iters)
+    traffic = measured_traffic() if iters == 1 else None
+    # achieved: the measurement table's per-unit figure for a PCG iteration (52 B per cell) over the
+    # measured mean iteration (above the memory's peak where the vectors stay on the chip);
+    # moved_bytes: what the launch must move
     sb = table_rule_bytes(dict(kernel="pcg_step", nodes=dom["nodes"], cells=dom["cells"], tag=1))
     s_gbps = sb / (dom["us_mean"] * 1e3)
     roofline = dict(bound="hbm", achieved=round(s_gbps, 1), peak=HBM_PEAK_GBPS, unit="GB/s",
                     frac=round(s_gbps / HBM_PEAK_GBPS, 4), traffic=traffic,
-                    kernel="k_pcg_step (finest level, 144x169x111 nodes, full PCG iterations)",
+                    kernel=(f"{'k_pcg_resident' if iters > 1 else 'k_pcg_step'} (finest level, "
+                            "144x169x111 nodes, full PCG iterations)"),
                     bytes_rule="52 B per cell per PCG iteration (HVP + CG vector updates)",
-                    bytes_per_launch=sb, us_per_launch=dom["us_mean"],
-                    us_median=dom["us_median"], launches=dom["launches"], grid=dom["grid"],
+                    bytes_per_launch=sb * iters, iterations_per_launch=iters,
+                    us_per_launch=round(dom["us_mean"] * iters, 3),
+                    us_median=round(dom["us_median"] * iters, 3), launches=dom["launches"], grid=dom["grid"],
                     moved_bytes=dict(bytes_rule=dom["bytes_rule"],
                                      bytes_per_launch=dom["bytes_per_launch"],
                                      achieved=dom["achieved_GBps"], frac=dom["frac"]),

@@ -238,7 +238,15 @@ rgp_status rgp_gn_hvp(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
 
 /* Jacobi-preconditioned CG for H_J x = rhs from x0 = 0 (Sec. 2.3.1): at most maxit iterations,
  * stopping early when |r| / |rhs| < rtol or when p^T H p <= 0.  x: field array written in full.
- * iters_dev (int32) and relres_dev (double): device outputs, nullable. */
+ * iters_dev (int32) and relres_dev (double): device outputs, nullable.
+ *
+ * Two forms of the same iteration.  A volume whose vectors fit the chip (about 5 M nodes in FP32,
+ * 0.9 M in FP64, at most 256 nodes along the contiguous axis) is solved by one launch that keeps
+ * them there; else, inside a caller's own stream capture, and while such a launch is still running
+ * on another stream of the device, one launch per iteration.  Their block sums are added in
+ * different orders, so results agree to rounding; each form by itself is bitwise reproducible.
+ * The solves inside rgp_correct, the plans and the batches choose in the same way (a plan holds
+ * both forms and chooses at each launch). */
 rgp_status rgp_pcg_solve(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
                          const void* hoff, double alpha, const void* rhs, void* x, int32_t maxit,
                          double rtol, int32_t* iters_dev, double* relres_dev, void* ws,
@@ -314,7 +322,8 @@ rgp_status rgp_plan_destroy(rgp_plan plan);
  * buffers corrected by one captured HIP graph (replayed with rgp_plan_launch) in which every
  * Gauss-Newton kernel - loss_grad, the PCG scalar phase and steps, the Armijo passes and
  * decisions, the step update - is ONE launch covering all pairs, each pair's workgroups reading
- * their arguments from a table in the workspace; the pyramid, OT, prolongation and correction
+ * their arguments from a table in the workspace (PCG solves in the one-launch form of
+ * rgp_pcg_solve: as few launches as hold the pairs; not where batch_march is set); the pyramid, OT, prolongation and correction
  * kernels run pair by pair inside the same graph.  Per pair the arithmetic is that of
  * rgp_correct (same options for all pairs; use_b_init must be 0; at most 1024 pairs; the
  * contiguous field axis of every pair at most 256 nodes, else RGP_ESHAPE).  I_plus, I_minus,
@@ -378,7 +387,8 @@ typedef enum {
   RGP_KERNEL_DHT = 7,        /* ADMM z-update: one Hartley pass along a cross axis (Sec. 2.3.2) */
   RGP_KERNEL_BLOCK_PCG = 8,  /* ADMM b-update: per-column Jacobi PCG (Sec. 2.3.2) */
   RGP_KERNEL_LBFGS = 9,      /* L-BFGS direction, one of its three phases (Sec. 2.3.3) */
-  RGP_KERNEL_LSQ = 10        /* least-squares correction, CGLS per column (Sec. 2.4.7) */
+  RGP_KERNEL_LSQ = 10,       /* least-squares correction, CGLS per column (Sec. 2.4.7) */
+  RGP_KERNEL_PCG_SOLVE = 11  /* a whole PCG solve in one launch (tag: its iteration limit) */
 } rgp_kernel_kind;
 typedef struct {
   int32_t kernel;

@@ -292,6 +292,74 @@ rgp_status check_opts(const rgp_solver_opts* o) {
   return RGP_OK;
 }
 
+// Whether resident launches may be issued on a stream now, and the note that they were.  Two of
+// them running side by side on one device would each wait for CUs that the other holds, so they
+// are issued only where the ones issued last are on the same stream or have finished; a call that
+// finds them running elsewhere takes the stepped form, and so does one inside a caller's own
+// capture, whose replays are not seen here.  One event per device, made at its first use.
+class ResidentTurn {
+ public:
+  explicit ResidentTurn(hipStream_t s) : s_(s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return;
+    int dev = 0;
+    hipDevice_t on = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return;
+    if (s && (hipStreamGetDevice(s, &on) != hipSuccess || (int)on != dev)) return;
+    // another thread may be capturing in a mode that forbids event calls everywhere
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+    {
+      std::lock_guard<std::mutex> lk(mu());
+      Device& d = devices()[dev];
+      if (d.cus < 0 &&
+          (hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+           hipEventCreateWithFlags(&d.last, hipEventDisableTiming) != hipSuccess))
+        d.cus = 0;
+      bool free = d.cus >= kMaxResUnits && !d.issuing;
+      if (free && d.any && d.stream != s) {
+        free = hipEventQuery(d.last) == hipSuccess;
+        if (!free) (void)hipGetLastError();
+      }
+      if (free) {
+        d.issuing = true;
+        d_ = &d;
+      }
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  ~ResidentTurn() {
+    if (!d_) return;
+    std::lock_guard<std::mutex> lk(mu());
+    (void)hipEventRecord(d_->last, s_);
+    d_->stream = s_;
+    d_->any = true;
+    d_->issuing = false;
+  }
+  ResidentTurn(const ResidentTurn&) = delete;
+  ResidentTurn& operator=(const ResidentTurn&) = delete;
+  bool mine() const { return d_ != nullptr; }
+
+ private:
+  static constexpr int kDevices = 64;
+  struct Device {
+    int cus = -1;
+    hipEvent_t last = nullptr;
+    hipStream_t stream = nullptr;
+    bool any = false, issuing = false;
+  };
+  static std::mutex& mu() {
+    static std::mutex m;
+    return m;
+  }
+  static Device* devices() {
+    static Device d[kDevices];
+    return d;
+  }
+  hipStream_t s_;
+  Device* d_ = nullptr;
+};
+
 // The Armijo passes of one step on the direction in w.X: gamma = 1 alone (it is accepted in most
 // steps), then the remaining candidates 2^-1 .. 2^-9 in one pass; a pass after an accepted step
 // exits at once.
@@ -518,15 +586,72 @@ hipError_t run_level_admm(const CorrectWs& w, const Geom& g, const int64_t m[3],
   return hipSuccess;
 }
 
+// The stepped PCG of one Gauss-Newton step: one launch per iteration (and one for the last update).
+hipError_t pcg_steps(const CorrectWs& w, const Geom& g, DType real, const rgp_solver_opts* o,
+                     const LossFinalArgs& lf, hipStream_t s) {
+  hipError_t e;
+  const Control& k = w.ctl;
+  const PcgPlan Lpcg = plan_pcg(g, real);
+  for (int i = 0; i <= o->pcg_iters; ++i) {
+    const int in = (i + 1) & 1, out = i & 1;
+    PcgScalarArgs sa{};
+    sa.st = k.st;
+    sa.slots = k.slots;
+    sa.part_prev = k.slot(kPartPcg0 + in);
+    sa.nprod = Lpcg.grid;
+    sa.iter = i;
+    sa.maxit = o->pcg_iters;
+    sa.rtol = o->pcg_rtol;
+    sa.gn_mode = 1;
+    sa.fused = Lpcg.fused;
+    sa.lf = lf;
+    if (!sa.fused && (e = launch_pcg_scalars(sa, s)) != hipSuccess) return e;
+    PcgArgs pa{};
+    pa.g = g;
+    pa.diag = w.Dg;
+    pa.off = w.Of;
+    pa.rhs = w.G;
+    pa.rhs_sign = -1.0;
+    pa.x = w.X;
+    pa.r_in = w.R[in];
+    pa.p_in = w.P[in];
+    pa.w_in = w.W[in];
+    pa.r_out = w.R[out];
+    pa.p_out = w.P[out];
+    pa.w_out = w.W[out];
+    pa.alpha = o->alpha;
+    pa.part = k.slot(kPartPcg0 + out);
+    pa.sc = sa;
+    if ((e = launch_pcg_step(pa, real, s)) != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// How a level runs its PCG solves.  solve: one entry of the launch sequence per solve, in the
+// resident form where that is set; else one launch per iteration.  tag: the next free tag of the
+// resident launches.
+struct PcgForm {
+  bool solve, resident;
+  uint32_t tag;
+};
+
+// Levels whose PCG solves may run in the resident form (bit l: level l).  From the coarsest on up
+// to the first that does not fit, so that no stepped level, which overwrites the exchange words,
+// comes before a resident one.
+uint32_t resident_levels(const Level* lv, int levels, DType real) {
+  uint32_t m = 0;
+  for (int l = levels - 1; l >= 0 && plan_resident(lv[l].g, real).ok; --l) m |= 1u << l;
+  return m;
+}
+
 // `gn_iters` Gauss-Newton steps on one level.  b enters in B[cur]; on return the final field is
 // in B[cur].
 hipError_t run_level(const CorrectWs& w, const Geom& g, const void* Ip, const void* Im, DType img,
                      DType real, const rgp_solver_opts* o, int& cur, double* records,
-                     hipStream_t s) {
+                     PcgForm& form, hipStream_t s) {
   hipError_t e;
   const Control& k = w.ctl;
   const Launch Llg = plan_loss_grad(g, real);
-  const PcgPlan Lpcg = plan_pcg(g, real);
   for (int it = 0; it < o->gn_iters; ++it) {
     const Range range("rgp: Gauss-Newton step %d", it);
     double* rec = records ? records + (size_t)it * kStatFields : nullptr;
@@ -549,39 +674,42 @@ hipError_t run_level(const CorrectWs& w, const Geom& g, const void* Ip, const vo
     if ((e = launch_loss_grad(la, img, real, s)) != hipSuccess) return e;
     if (it > 0) cur = 1 - cur;
 
-    for (int i = 0; i <= o->pcg_iters; ++i) {
-      const int in = (i + 1) & 1, out = i & 1;
-      PcgScalarArgs sa{};
-      sa.st = k.st;
-      sa.slots = k.slots;
-      sa.part_prev = k.slot(kPartPcg0 + in);
-      sa.nprod = Lpcg.grid;
-      sa.iter = i;
-      sa.maxit = o->pcg_iters;
-      sa.rtol = o->pcg_rtol;
-      sa.gn_mode = 1;
-      sa.fused = Lpcg.fused;
-      sa.lf = LossFinalArgs{k.slot(kPartLoss), Llg.grid, g.vol, o->alpha, o->beta, k.st,
-                            nullptr, rec, 1};
-      if (!sa.fused && (e = launch_pcg_scalars(sa, s)) != hipSuccess) return e;
-      PcgArgs pa{};
-      pa.g = g;
-      pa.diag = w.Dg;
-      pa.off = w.Of;
-      pa.rhs = w.G;
-      pa.rhs_sign = -1.0;
-      pa.x = w.X;
-      pa.r_in = w.R[in];
-      pa.p_in = w.P[in];
-      pa.w_in = w.W[in];
-      pa.r_out = w.R[out];
-      pa.p_out = w.P[out];
-      pa.w_out = w.W[out];
-      pa.alpha = o->alpha;
-      pa.part = k.slot(kPartPcg0 + out);
-      pa.sc = sa;
-      if ((e = launch_pcg_step(pa, real, s)) != hipSuccess) return e;
+    const LossFinalArgs lf{k.slot(kPartLoss), Llg.grid, g.vol, o->alpha, o->beta, k.st, nullptr,
+                           rec, 1};
+    if (form.solve) {
+      if (form.resident) {
+        const ResPlan R = plan_resident(g, real);
+        ResArgs ra = make_res_args(g, R, o->alpha);
+        ra.diag = w.Dg;
+        ra.off = w.Of;
+        ra.rhs = w.G;
+        ra.x = w.X;
+        ra.words = static_cast<unsigned long long*>(w.R[0]);
+        ra.part = reinterpret_cast<unsigned long long*>(k.slot(kPartPcg0));
+        ra.sync = ra.part + kResSumWords;
+        ra.spare_r = w.P[1];
+        ra.spare_p = w.W[1];
+        ra.rhs_sign = -1.0;
+        ra.rtol = o->pcg_rtol;
+        ra.st = k.st;
+        ra.lf = lf;
+        ra.gn_mode = 1;
+        ra.maxit = o->pcg_iters;
+        ra.tag = form.tag;
+        form.tag += (uint32_t)o->pcg_iters + 1u;
+        e = launch_pcg_resident_one(ra, R, real, s);
+      } else {
+        // (recording only) several stepped launches as one entry of a batch's sequence
+        const CorrectWs wc = w;
+        const rgp_solver_opts oc = *o;
+        e = record_solve([wc, g, real, oc, lf](hipStream_t s2) {
+          return pcg_steps(wc, g, real, &oc, lf, s2);
+        });
+      }
+    } else {
+      e = pcg_steps(w, g, real, o, lf, s);
     }
+    if (e != hipSuccess) return e;
 
     if ((e = armijo_passes(w, g, Ip, Im, img, real, o, w.B[cur], w.G, rec, s)) != hipSuccess)
       return e;
@@ -947,6 +1075,32 @@ rgp_status rgp_pcg_solve(const rgp_grid* grid, rgp_dtype real_t, const void* hdi
   Control k = carve_control(c);
   void* vec[6];
   for (int i = 0; i < 6; ++i) vec[i] = c.take(g.nnode * dsize(dr));
+  const ResPlan R = plan_resident(g, dr);
+  if (R.ok) {
+    const ResidentTurn turn(s);
+    if (turn.mine()) {
+      ResArgs ra = make_res_args(g, R, alpha);
+      ra.diag = hdiag;
+      ra.off = hoff;
+      ra.rhs = rhs;
+      ra.x = x;
+      ra.words = static_cast<unsigned long long*>(vec[0]);
+      ra.part = reinterpret_cast<unsigned long long*>(k.slot(kPartPcg0));
+      ra.sync = ra.part + kResSumWords;
+      ra.spare_r = vec[4];
+      ra.spare_p = vec[5];
+      ra.rhs_sign = 1.0;
+      ra.rtol = rtol;
+      ra.st = k.st;
+      ra.iters_out = iters_dev;
+      ra.relres_out = relres_dev;
+      ra.maxit = maxit;
+      ra.tag = 1;
+      RGP_HIP(launch_clear_words(vec[0], g.nnode, dr, ra.part, s));
+      RGP_HIP(launch_pcg_resident_one(ra, R, dr, s));
+      return RGP_OK;
+    }
+  }
   const PcgPlan L = plan_pcg(g, dr);
   for (int i = 0; i <= maxit; ++i) {
     const int in = (i + 1) & 1, out = i & 1;
@@ -1080,7 +1234,7 @@ hipError_t copy_d2d(void* dst, const void* src, size_t bytes, hipStream_t s) {
 rgp_status enqueue_correct(const rgp_grid* grid, rgp_dtype img_t, const void* I_plus,
                            const void* I_minus, rgp_dtype real_t, const rgp_solver_opts* opts,
                            const void* b_init, void* b_out, void* T_plus, void* T_minus,
-                           double* stats_dev, void* ws, hipStream_t s) {
+                           double* stats_dev, void* ws, uint32_t solve_levels, hipStream_t s) {
   DType di, dr;
   dtype_of(img_t, &di);
   dtype_of(real_t, &dr);
@@ -1158,8 +1312,18 @@ rgp_status enqueue_correct(const rgp_grid* grid, rgp_dtype img_t, const void* I_
     RGP_HIP(launch_blur(ba, dr, s));
     cur = 1;
   }
+  const uint32_t resident = resident_levels(lv, L, dr) & solve_levels;
+  if (solve_levels) {   // the exchange words, once for every resident launch of this solve
+    int64_t nodes = 0;
+    for (int l = 0; l < L; ++l)
+      if (resident >> l & 1u) nodes = std::max(nodes, lv[l].g.nnode);
+    RGP_HIP(launch_clear_words(w.R[0], nodes, dr, w.ctl.slot(kPartPcg0), s));
+  }
+  PcgForm form{false, false, 1u};
   for (int l = L - 1; l >= 0; --l) {
     const Range rl("rgp: level %d", l);
+    form.solve = (solve_levels >> l & 1u) != 0;
+    form.resident = (resident >> l & 1u) != 0;
     if (l < L - 1) {
       ProlongArgs pa{};
       pa.src = w.B[cur];
@@ -1182,7 +1346,7 @@ rgp_status enqueue_correct(const rgp_grid* grid, rgp_dtype img_t, const void* I_
       e = run_level_admm(w, lv[l].g, lv[l].m, grid->pe, lv[l].h, imgs[l][0], imgs[l][1],
                          ity[l], dr, opts, cur, rec, s);
     else
-      e = run_level(w, lv[l].g, imgs[l][0], imgs[l][1], ity[l], dr, opts, cur, rec, s);
+      e = run_level(w, lv[l].g, imgs[l][0], imgs[l][1], ity[l], dr, opts, cur, rec, form, s);
     if (e != hipSuccess) {
       g_last_hip = (int)e;
       return RGP_EHIP;
@@ -1206,10 +1370,67 @@ rgp_status enqueue_correct(const rgp_grid* grid, rgp_dtype img_t, const void* I_
 
 }  // namespace
 
-struct rgp_plan_s {
-  hipGraph_t graph;
-  hipGraphExec_t exec;
+namespace {
+struct CapturedGraph {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
 };
+hipError_t release(CapturedGraph& g) {
+  const hipError_t e1 = g.exec ? hipGraphExecDestroy(g.exec) : hipSuccess;
+  const hipError_t e2 = g.graph ? hipGraphDestroy(g.graph) : hipSuccess;
+  g = CapturedGraph{};
+  return e1 != hipSuccess ? e1 : e2;
+}
+}  // namespace
+
+// A plan holds the sequence in both forms of the PCG (resident only where a level fits it); each
+// launch takes the one that the device's other work allows (ResidentTurn).
+struct rgp_plan_s {
+  CapturedGraph resident, stepped;
+};
+
+namespace {
+
+// Captures what `issue(resident)` enqueues on s, once or in both forms, into a new plan.
+template <typename F>
+rgp_status make_plan(hipStream_t s, bool resident, rgp_plan* plan, F issue) {
+  CapturedGraph g[2];
+  rgp_status st = RGP_OK;
+  for (int f = 0; f < (resident ? 2 : 1) && st == RGP_OK; ++f) {
+    hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+      st = issue(f == 1);
+      e = hipStreamEndCapture(s, &g[f].graph);
+    }
+    if (e == hipSuccess && st == RGP_OK)
+      e = hipGraphInstantiate(&g[f].exec, g[f].graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) {
+      g_last_hip = (int)e;
+      if (st == RGP_OK) st = RGP_EHIP;
+    }
+  }
+  rgp_plan p = st == RGP_OK ? new (std::nothrow) rgp_plan_s{g[1], g[0]} : nullptr;
+  if (!p) {
+    (void)release(g[0]);
+    (void)release(g[1]);
+    return st == RGP_OK ? RGP_EINVAL : st;
+  }
+  *plan = p;
+  return RGP_OK;
+}
+
+uint32_t grid_resident_levels(const rgp_grid* grid, const rgp_solver_opts* o, rgp_dtype real_t) {
+  DType dr;
+  Level lv[kMaxLevels];
+  if (o->solver != RGP_SOLVER_GN || o->gn_iters < 1 || !dtype_of(real_t, &dr) ||
+      make_levels(grid, o->levels, lv) != 0)
+    return 0;
+  // every resident launch of a solve has its own tags
+  if ((int64_t)o->levels * o->gn_iters * (o->pcg_iters + 1) >= (int64_t(1) << 31)) return 0;
+  return resident_levels(lv, o->levels, dr);
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -1220,8 +1441,16 @@ rgp_status rgp_correct(const rgp_grid* grid, rgp_dtype img_t, const void* I_plus
   rgp_status st = check_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, ws,
                                 ws_bytes);
   if (st != RGP_OK) return st;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const uint32_t resident = grid_resident_levels(grid, opts, real_t);
+  if (resident) {
+    const ResidentTurn turn(s);
+    if (turn.mine())
+      return enqueue_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, T_plus,
+                             T_minus, stats_dev, ws, resident, s);
+  }
   return enqueue_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, T_plus,
-                         T_minus, stats_dev, ws, static_cast<hipStream_t>(stream));
+                         T_minus, stats_dev, ws, 0u, s);
 }
 
 rgp_status rgp_correct_plan(const rgp_grid* grid, rgp_dtype img_t, const void* I_plus,
@@ -1236,43 +1465,30 @@ rgp_status rgp_correct_plan(const rgp_grid* grid, rgp_dtype img_t, const void* I
                                 ws_bytes);
   if (st != RGP_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  RGP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-  st = enqueue_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, T_plus, T_minus,
-                       stats_dev, ws, s);
-  hipGraph_t graph = nullptr;
-  const hipError_t e = hipStreamEndCapture(s, &graph);
-  if (st != RGP_OK || e != hipSuccess) {
-    if (graph) (void)hipGraphDestroy(graph);
-    if (e != hipSuccess) g_last_hip = (int)e;
-    return st != RGP_OK ? st : RGP_EHIP;
-  }
-  hipGraphExec_t exec = nullptr;
-  const hipError_t e2 = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (e2 != hipSuccess) {
-    (void)hipGraphDestroy(graph);
-    g_last_hip = (int)e2;
-    return RGP_EHIP;
-  }
-  rgp_plan p = new (std::nothrow) rgp_plan_s{graph, exec};
-  if (!p) {
-    (void)hipGraphExecDestroy(exec);
-    (void)hipGraphDestroy(graph);
-    return RGP_EINVAL;
-  }
-  *plan = p;
-  return RGP_OK;
+  return make_plan(s, grid_resident_levels(grid, opts, real_t) != 0, plan, [&](bool resident) {
+    return enqueue_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, T_plus,
+                           T_minus, stats_dev, ws,
+                           resident ? grid_resident_levels(grid, opts, real_t) : 0u, s);
+  });
 }
 
 rgp_status rgp_plan_launch(rgp_plan plan, void* stream) {
   if (!plan) return RGP_EINVAL;
-  RGP_HIP(hipGraphLaunch(plan->exec, static_cast<hipStream_t>(stream)));
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  if (plan->resident.exec) {
+    const ResidentTurn turn(s);
+    if (turn.mine()) {
+      RGP_HIP(hipGraphLaunch(plan->resident.exec, s));
+      return RGP_OK;
+    }
+  }
+  RGP_HIP(hipGraphLaunch(plan->stepped.exec, s));
   return RGP_OK;
 }
 
 rgp_status rgp_plan_destroy(rgp_plan plan) {
   if (!plan) return RGP_OK;
-  const hipError_t e1 = hipGraphExecDestroy(plan->exec);
-  const hipError_t e2 = hipGraphDestroy(plan->graph);
+  const hipError_t e1 = release(plan->resident), e2 = release(plan->stepped);
   delete plan;
   if (e1 != hipSuccess || e2 != hipSuccess) {
     g_last_hip = (int)(e1 != hipSuccess ? e1 : e2);
@@ -1434,16 +1650,65 @@ struct BatchSlot {
   int var[4] = {0, 0, 0, 0};
   int64_t cells = 0, nodes = 0;  // summed over the pairs (kernel timing)
   int tag = 0;
+  std::vector<ResidentLaunch> solves;  // kPcgSolve: the pairs' resident solves, packed
 };
 
-// Records the correction of every pair (their workspaces laid out back to back from ws) and
-// merges the sequences: returns the per-pair launches and the table arena.
+// The merged sequence of a batch: the pairs' launches, how each is issued, and the argument tables
+// of the shared ones.
+struct BatchSequence {
+  std::vector<Recorder> recs;
+  std::vector<BatchSlot> slots;
+  std::vector<unsigned char> arena;
+  unsigned char* arena_dev = nullptr;
+};
+
+// Levels whose PCG solves are single entries of the pairs' sequences: those that some pair runs in
+// the resident form (a pair that does not fit it there issues its stepped launches by itself).
+// None when the caller asks for a march length, which is the stepped form's.
+uint32_t batch_solve_levels(int32_t n, const rgp_grid* grids, rgp_dtype real_t,
+                            const rgp_solver_opts* o) {
+  uint32_t m = 0;
+  if (o->batch_march == 0)
+    for (int p = 0; p < n; ++p) m |= grid_resident_levels(&grids[p], o, real_t);
+  return m;
+}
+
+// Packs launch i of the pairs, in order, into launches of at most one workgroup per CU.
+void pack_solves(const std::vector<Recorder>& recs, size_t i, std::vector<ResidentLaunch>& out) {
+  for (const Recorder& rec : recs) {
+    const RecLaunch& r = rec.launches[i];
+    if (r.args.empty()) continue;
+    ResArgs a;
+    std::memcpy(&a, r.args.data(), sizeof(a));
+    size_t k = 0;   // the first launch of the same kernel variant with room
+    while (k < out.size() &&
+           (out[k].tier != r.var[1] || out[k].real != (DType)r.var[0] ||
+            out[k].b.n == kMaxResVolumes || out[k].b.start[out[k].b.n] + a.units > kMaxResUnits))
+      ++k;
+    if (k == out.size()) {
+      out.push_back(ResidentLaunch{});
+      out[k].real = (DType)r.var[0];
+      out[k].tier = r.var[1];
+    }
+    ResidentLaunch& l = out[k];
+    l.b.v[l.b.n] = a;
+    l.b.start[l.b.n + 1] = l.b.start[l.b.n] + a.units;
+    ++l.b.n;
+    l.lds = std::max(l.lds, r.lds);
+  }
+}
+
+// Records the correction of every pair (their workspaces laid out back to back from ws; levels in
+// solve_levels with one entry per PCG solve) and merges the sequences: returns the per-pair
+// launches and the table arena.
 rgp_status record_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
                         const void* const* I_plus, const void* const* I_minus, rgp_dtype real_t,
                         const rgp_solver_opts* opts, void* const* b_out, void* const* T_plus,
                         void* const* T_minus, double* const* stats, unsigned char* ws,
-                        std::vector<Recorder>& recs, std::vector<BatchSlot>& slots,
-                        std::vector<unsigned char>& arena, size_t& pairs_total) {
+                        uint32_t solve_levels, BatchSequence& seq, size_t& pairs_total) {
+  std::vector<Recorder>& recs = seq.recs;
+  std::vector<BatchSlot>& slots = seq.slots;
+  std::vector<unsigned char>& arena = seq.arena;
   DType dr;
   dtype_of(real_t, &dr);
   recs.assign((size_t)n, Recorder{});
@@ -1455,7 +1720,7 @@ rgp_status record_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
       rgp_status st = enqueue_correct(&grids[p], img_t, I_plus[p], I_minus[p], real_t, opts,
                                       nullptr, b_out[p], T_plus ? T_plus[p] : nullptr,
                                       T_minus ? T_minus[p] : nullptr, stats ? stats[p] : nullptr,
-                                      ws + off, nullptr);
+                                      ws + off, solve_levels, nullptr);
       if (st != RGP_OK) return st;
       off += pair_bytes(&grids[p], opts, dr);
     }
@@ -1487,6 +1752,10 @@ rgp_status record_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
       for (int p = 1; p < n; ++p)
         if (recs[(size_t)p].launches[i].kind != r0.kind) return RGP_EINVAL;
     }
+    if (r0.kind == RecKind::kPcgSolve) {
+      pack_solves(recs, i, sl.solves);
+      continue;
+    }
     if (r0.kind == RecKind::kOther || n == 1 || !same) continue;
     sl.shared = true;
     std::copy(r0.var, r0.var + 4, sl.var);
@@ -1513,12 +1782,38 @@ rgp_status record_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
   return RGP_OK;
 }
 
-hipError_t issue_batch(int32_t n, const std::vector<Recorder>& recs,
-                       const std::vector<BatchSlot>& slots, const unsigned char* arena_dev,
-                       hipStream_t s) {
+// Records the batch with one launch per PCG iteration and, where some level has that form, with
+// resident solves.
+rgp_status record_forms(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
+                        const void* const* I_plus, const void* const* I_minus, rgp_dtype real_t,
+                        const rgp_solver_opts* opts, void* const* b_out, void* const* T_plus,
+                        void* const* T_minus, double* const* stats, unsigned char* ws,
+                        BatchSequence (&seq)[2], size_t& pairs_total) {
+  const uint32_t solve_levels = batch_solve_levels(n, grids, real_t, opts);
+  for (int f = 0; f < (solve_levels ? 2 : 1); ++f) {
+    const rgp_status st =
+        record_batch(n, grids, img_t, I_plus, I_minus, real_t, opts, b_out, T_plus, T_minus, stats,
+                     ws, f ? solve_levels : 0u, seq[f], pairs_total);
+    if (st != RGP_OK) return st;
+  }
+  return RGP_OK;
+}
+
+hipError_t issue_batch(int32_t n, const BatchSequence& seq, hipStream_t s) {
+  const std::vector<Recorder>& recs = seq.recs;
+  const std::vector<BatchSlot>& slots = seq.slots;
+  const unsigned char* arena_dev = seq.arena_dev;
   for (size_t i = 0; i < slots.size(); ++i) {
     const BatchSlot& sl = slots[i];
     hipError_t e = hipSuccess;
+    if (sl.kind == RecKind::kPcgSolve) {
+      for (const ResidentLaunch& l : sl.solves)
+        if ((e = launch_pcg_resident(l.b, l.real, l.tier, l.lds, s)) != hipSuccess) return e;
+      for (int p = 0; p < n && e == hipSuccess; ++p)
+        if (recs[(size_t)p].launches[i].args.empty()) e = recs[(size_t)p].launches[i].replay(s);
+      if (e != hipSuccess) return e;
+      continue;
+    }
     if (!sl.shared) {
       for (int p = 0; p < n && e == hipSuccess; ++p) e = recs[(size_t)p].launches[i].replay(s);
       if (e != hipSuccess) return e;
@@ -1567,27 +1862,25 @@ rgp_status rgp_batch_workspace_size(int32_t n, const rgp_grid* grids, rgp_dtype 
   // a dry recording with placeholder addresses gives the size of the launch tables
   std::vector<const void*> img((size_t)n, reinterpret_cast<const void*>(kAlign));
   std::vector<void*> out((size_t)n, reinterpret_cast<void*>(kAlign));
-  std::vector<Recorder> recs;
-  std::vector<BatchSlot> slots;
-  std::vector<unsigned char> arena;
+  BatchSequence seq[2];
   size_t pairs = 0;
-  st = record_batch(n, grids, RGP_F32, img.data(), img.data(), real_t, opts, out.data(), nullptr,
-                    nullptr, nullptr, nullptr, recs, slots, arena, pairs);
+  st = record_forms(n, grids, RGP_F32, img.data(), img.data(), real_t, opts, out.data(), nullptr,
+                    nullptr, nullptr, nullptr, seq, pairs);
   if (st != RGP_OK) return st;
-  *bytes = pairs + arena.size();
+  *bytes = pairs + seq[0].arena.size() + seq[1].arena.size();
   return RGP_OK;
 }
 
 namespace {
 
-// Checks the arguments of a batched correction, records every pair's sequence and uploads the
-// shared launches' tables to the workspace (synchronising `s` once: the host tables die here).
+// Checks the arguments of a batched correction, records every pair's sequence (seq[0] stepped,
+// seq[1] resident where some level has that form) and uploads the shared launches' tables to the
+// workspace (synchronising `s` once: the host tables die here).
 rgp_status prepare_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
                          const void* const* I_plus, const void* const* I_minus, rgp_dtype real_t,
                          const rgp_solver_opts* opts, void* const* b_out, void* const* T_plus,
                          void* const* T_minus, double* const* stats_dev, void* ws, size_t ws_bytes,
-                         hipStream_t s, std::vector<Recorder>& recs,
-                         std::vector<BatchSlot>& slots, unsigned char** arena_dev) {
+                         hipStream_t s, BatchSequence (&seq)[2]) {
   rgp_status st = check_batch_grids(n, grids, real_t, opts);
   if (st != RGP_OK) return st;
   DType di, dr;
@@ -1602,16 +1895,17 @@ rgp_status prepare_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
   if ((st = rgp_batch_workspace_size(n, grids, real_t, opts, &need)) != RGP_OK) return st;
   if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) % kAlign) != 0)
     return RGP_EWORKSPACE;
-  std::vector<unsigned char> arena;
-  size_t pairs = 0;
-  st = record_batch(n, grids, img_t, I_plus, I_minus, real_t, opts, b_out, T_plus, T_minus,
-                    stats_dev, static_cast<unsigned char*>(ws), recs, slots, arena, pairs);
+  size_t at = 0;
+  st = record_forms(n, grids, img_t, I_plus, I_minus, real_t, opts, b_out, T_plus, T_minus,
+                    stats_dev, static_cast<unsigned char*>(ws), seq, at);
   if (st != RGP_OK) return st;
-  *arena_dev = static_cast<unsigned char*>(ws) + pairs;
-  if (!arena.empty()) {
-    RGP_HIP(hipMemcpyAsync(*arena_dev, arena.data(), arena.size(), hipMemcpyHostToDevice, s));
-    RGP_HIP(hipStreamSynchronize(s));
+  for (BatchSequence& q : seq) {
+    q.arena_dev = static_cast<unsigned char*>(ws) + at;
+    at += q.arena.size();
+    if (!q.arena.empty())
+      RGP_HIP(hipMemcpyAsync(q.arena_dev, q.arena.data(), q.arena.size(), hipMemcpyHostToDevice, s));
   }
+  if (!seq[0].arena.empty() || !seq[1].arena.empty()) RGP_HIP(hipStreamSynchronize(s));
   return RGP_OK;
 }
 
@@ -1626,13 +1920,18 @@ rgp_status rgp_correct_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   RGP_HIP(hipStreamIsCapturing(s, &cs));
   if (cs != hipStreamCaptureStatusNone) return RGP_EINVAL;  // it synchronises the stream
-  std::vector<Recorder> recs;
-  std::vector<BatchSlot> slots;
-  unsigned char* arena_dev = nullptr;
+  BatchSequence seq[2];
   rgp_status st = prepare_batch(n, grids, img_t, I_plus, I_minus, real_t, opts, b_out, T_plus,
-                                T_minus, stats_dev, ws, ws_bytes, s, recs, slots, &arena_dev);
+                                T_minus, stats_dev, ws, ws_bytes, s, seq);
   if (st != RGP_OK) return st;
-  RGP_HIP(issue_batch(n, recs, slots, arena_dev, s));
+  if (!seq[1].slots.empty()) {
+    const ResidentTurn turn(s);
+    if (turn.mine()) {
+      RGP_HIP(issue_batch(n, seq[1], s));
+      return RGP_OK;
+    }
+  }
+  RGP_HIP(issue_batch(n, seq[0], s));
   return RGP_OK;
 }
 
@@ -1646,36 +1945,16 @@ rgp_status rgp_correct_batch_plan(int32_t n, const rgp_grid* grids, rgp_dtype im
   *plan = nullptr;
   if (!stream) return RGP_EINVAL;  // the legacy default stream cannot be captured
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  std::vector<Recorder> recs;
-  std::vector<BatchSlot> slots;
-  unsigned char* arena_dev = nullptr;
+  BatchSequence seq[2];
   rgp_status st = prepare_batch(n, grids, img_t, I_plus, I_minus, real_t, opts, b_out, T_plus,
-                                T_minus, stats_dev, ws, ws_bytes, s, recs, slots, &arena_dev);
+                                T_minus, stats_dev, ws, ws_bytes, s, seq);
   if (st != RGP_OK) return st;
-  RGP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-  const hipError_t e = issue_batch(n, recs, slots, arena_dev, s);
-  hipGraph_t graph = nullptr;
-  const hipError_t e1 = hipStreamEndCapture(s, &graph);
-  if (e != hipSuccess || e1 != hipSuccess) {
-    if (graph) (void)hipGraphDestroy(graph);
-    g_last_hip = (int)(e != hipSuccess ? e : e1);
+  return make_plan(s, !seq[1].slots.empty(), plan, [&](bool resident) {
+    const hipError_t e = issue_batch(n, seq[resident ? 1 : 0], s);
+    if (e == hipSuccess) return RGP_OK;
+    g_last_hip = (int)e;
     return RGP_EHIP;
-  }
-  hipGraphExec_t exec = nullptr;
-  const hipError_t e2 = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (e2 != hipSuccess) {
-    (void)hipGraphDestroy(graph);
-    g_last_hip = (int)e2;
-    return RGP_EHIP;
-  }
-  rgp_plan pl = new (std::nothrow) rgp_plan_s{graph, exec};
-  if (!pl) {
-    (void)hipGraphExecDestroy(exec);
-    (void)hipGraphDestroy(graph);
-    return RGP_EINVAL;
-  }
-  *plan = pl;
-  return RGP_OK;
+  });
 }
 
 // ---- autotuner of the PCG march ----------------------------------------------------------

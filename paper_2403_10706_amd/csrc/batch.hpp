@@ -23,7 +23,8 @@ enum class RecKind : int {
   kDecide,
   kApply,
   kPcgScalars,
-  kPcgStep
+  kPcgStep,
+  kPcgSolve   // a whole solve: resident (args: ResArgs) or stepped (no args, replay only)
 };
 
 struct RecLaunch {
@@ -82,6 +83,22 @@ inline hipError_t record_other(std::function<hipError_t(hipStream_t)> replay) {
   active_recorder()->launches.push_back(std::move(r));
   return hipSuccess;
 }
+
+inline hipError_t record_solve(std::function<hipError_t(hipStream_t)> replay) {
+  RecLaunch r;
+  r.kind = RecKind::kPcgSolve;
+  r.replay = std::move(replay);
+  active_recorder()->launches.push_back(std::move(r));
+  return hipSuccess;
+}
+
+// One resident launch over several volumes.
+struct ResidentLaunch {
+  ResBatch b{};
+  DType real = DType::F32;
+  int tier = 0;
+  size_t lds = 0;
+};
 
 // Shared launches: tab points to n argument blocks in device memory, starts to n+1 workgroup
 // offsets (one workgroup per volume for the single-block kernels).  cells/nodes/tag: the summed

@@ -190,6 +190,47 @@ struct PcgPlan {
   int fused;               // scalar phase inside k_pcg_step (else one k_pcg_scalars per iteration)
 };
 
+// Resident PCG (pcg_resident.hip): one volume's solve by `units` co-resident workgroups.
+constexpr int kMaxResUnits = 256;        // one workgroup per CU
+constexpr int kMaxResVolumes = 12;       // volumes of one launch (their arguments travel by value)
+constexpr size_t kMaxResLds = 156 * 1024;
+constexpr int kResSumStride = 16;        // words of one unit's seven sums: a line of its own
+constexpr int kResSumWords = 2 * kResSumStride * kMaxResUnits;
+constexpr int kResSyncWords = kResSumWords + kMaxResUnits + 1;
+struct ResArgs {
+  const void* diag;
+  const void* off;
+  const void* rhs;
+  void* x;
+  unsigned long long* words;  // exchanged p: two parities of one word per 32 bits of the field
+  unsigned long long* part;   // exchanged sums: two parities of [kMaxResUnits][kResSumStride]
+  unsigned long long* sync;   // arrivals [kMaxResUnits], then the decision
+  void* spare_r;              // two vectors outside `words` (the solve by one workgroup)
+  void* spare_p;
+  double rhs_sign, cx, cy, rtol;
+  State* st;
+  int32_t* iters_out;         // nullable
+  double* relres_out;         // nullable
+  LossFinalArgs lf;           // gn_mode: J, D, S, P of the current iterate
+  int32_t gn_mode, maxit;
+  uint32_t tag;               // first tag of this launch (tag .. tag + maxit are its own)
+  int32_t no, na, nb, role, P, T, XL, noc, units;
+  uint32_t nnode, ncell;
+  FastDiv by_2nb;
+};
+struct ResBatch {
+  int32_t n;
+  int32_t start[kMaxResVolumes + 1];
+  ResArgs v[kMaxResVolumes];
+};
+static_assert(sizeof(ResBatch) <= 4096, "kernel arguments");
+struct ResPlan {
+  bool ok;      // the volume fits
+  MarchGeo m;
+  size_t lds;
+  int tier;     // the kernel variant
+};
+
 struct ShiftArgs {
   const void* Ip;
   const void* Im;
@@ -254,8 +295,8 @@ unsigned shift_grid(int64_t n);
 // is not being captured, timing_slot hands out a pair of HIP events that hipExtLaunchKernelGGL
 // records at the start and the end of the kernel itself, and notes the launch (tag: the PCG
 // iteration of a PCG step, the candidate count of a trial pass, the pass mode plus 4 times the
-// line length of a Hartley pass, the iteration limit of a block PCG, the phase of an L-BFGS
-// launch, else 0).
+// line length of a Hartley pass, the iteration limit of a block PCG or a resident PCG, the phase of
+// an L-BFGS launch, else 0).
 enum KernelKind : int {
   kKindPcgStep = 0,
   kKindLossGrad = 1,
@@ -268,7 +309,8 @@ enum KernelKind : int {
   kKindBlockPcg = 8,
   kKindLbfgs = 9,
   kKindLsq = 10,
-  kKindCount = 11
+  kKindPcgSolve = 11,
+  kKindCount = 12
 };
 bool timing_slot(int kind, int tag, unsigned grid, int64_t cells, int64_t nodes, hipStream_t s,
                  hipEvent_t* e0, hipEvent_t* e1);
@@ -436,6 +478,14 @@ hipError_t launch_sum_final(const double* part, unsigned nprod, double* out, hip
 hipError_t launch_pcg_step(const PcgArgs& a, DType real, hipStream_t s);
 hipError_t launch_pcg_step_plan(const PcgArgs& a, DType real, const PcgPlan& L, hipStream_t s);
 hipError_t launch_pcg_scalars(const PcgScalarArgs& a, hipStream_t s);
+constexpr size_t dsize_real(DType t) { return t == DType::F64 ? 8 : 4; }
+ResPlan plan_resident(const Geom& g, DType real);
+ResArgs make_res_args(const Geom& g, const ResPlan& L, double alpha);
+// Clears the exchange words of a volume of nnode nodes and the sums and arrivals at `sync`
+// (kResSyncWords words) before the first resident launch of a solve.
+hipError_t launch_clear_words(void* words, int64_t nnode, DType real, void* sync, hipStream_t s);
+hipError_t launch_pcg_resident_one(const ResArgs& a, const ResPlan& L, DType real, hipStream_t s);
+hipError_t launch_pcg_resident(const ResBatch& b, DType real, int tier, size_t lds, hipStream_t s);
 hipError_t launch_shift(const ShiftArgs& a, DType img, hipStream_t s);
 // Sets st->status to RGP_ENONFINITE when the input scan (the shift kernel's block sums) found a
 // non-finite image value.
