@@ -20,6 +20,8 @@
 // at once when the level has stopped (failed line search or barrier).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "batch.hpp"
 #include "rgp_internal.hpp"
 #include "rgp_launch.hpp"
@@ -29,7 +31,8 @@ namespace rgp {
 
 namespace {
 
-constexpr int kLbBlock = 256;
+constexpr int kLbBlock = 512;
+constexpr int kLbWaves = kLbBlock / kWave;
 
 __device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -54,7 +57,39 @@ __device__ __forceinline__ double block_max(double v) {
   return r;
 }
 
+// Sums of v over the workgroup (wavefronts in order): thread k < K gets sum k.
+template <int K>
+__device__ __forceinline__ double block_sum_k(double (&v)[K]) {
+  __shared__ double sh[kLbWaves][K];
+  wave_sums<K>(v);
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[threadIdx.x / kWave][k] = v[k];
+  }
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x < K) {
+    s = sh[0][threadIdx.x];
+#pragma unroll
+    for (int j = 1; j < kLbWaves; ++j) s += sh[j][threadIdx.x];
+  }
+  __syncthreads();   // the buffer may be reused by the next call
+  return s;
+}
+
 constexpr int kLbChunk = 4;   // window pairs per pass of kLbDots
+constexpr int kLbUnroll = 4;  // elements of a thread whose loads are in flight together
+
+// body(length constant, first index) over lo, lo + kLbBlock, ... below hi, kLbUnroll of them at a
+// time (one workgroup per CU must cover the latency: with one element at a time the 11 pairs of
+// 144x169x111 nodes took 155 us, 1.5 TB/s).
+template <typename F>
+__device__ __forceinline__ void for_range(int64_t lo, int64_t hi, F body) {
+  int64_t i = lo;
+  for (; i + (kLbUnroll - 1) * kLbBlock < hi; i += kLbUnroll * kLbBlock)
+    body(std::integral_constant<int, kLbUnroll>(), i);
+  for (; i < hi; i += kLbBlock) body(std::integral_constant<int, 1>(), i);
+}
 
 template <typename TR>
 __device__ void lbfgs_dots(const LbfgsArgs& a) {
@@ -76,26 +111,33 @@ __device__ void lbfgs_dots(const LbfgsArgs& a) {
   const TR gam = pair ? (TR)a.st->gamma : TR(0);
   double v3[3] = {0.0, 0.0, 0.0};
   double gmax = 0.0;
-  for (int64_t i = lo + t; i < hi; i += kLbBlock) {
-    const TR gi = g[i];
-    gmax = fmax(gmax, fabs((double)gi));
-    if (pair) {
-      const TR si = gam * x[i], yi = gi - go[i];
-      sh[i] = si;
-      yh[i] = yi;
+  for_range(lo + t, hi, [&](auto len, int64_t i) {
+    constexpr int L = decltype(len)::value;
+    TR gi[L], xi[L], oi[L];
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+      const int64_t k = i + u * kLbBlock;
+      gi[u] = g[k];
+      xi[u] = pair ? x[k] : TR(0);
+      oi[u] = pair ? go[k] : TR(0);
+    }
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+      gmax = fmax(gmax, fabs((double)gi[u]));
+      if (!pair) continue;
+      const TR si = gam * xi[u], yi = gi[u] - oi[u];
+      sh[i + u * kLbBlock] = si;
+      yh[i + u * kLbBlock] = yi;
       const double sd = (double)si, yd = (double)yi;
       v3[0] = fma(sd, yd, v3[0]);
       v3[1] = fma(yd, yd, v3[1]);
       v3[2] = fma(sd, sd, v3[2]);
     }
-  }
-  block_sum<3, kLbBlock>(v3);
+  });
+  const double s3 = block_sum_k<3>(v3);
   const double bm = block_max(gmax);
-  if (t == 0) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) a.part[(size_t)q * kMaxGrid + blockIdx.x] = v3[q];
-    a.part_max[blockIdx.x] = bm;
-  }
+  if (t < 3) a.part[(size_t)t * kMaxGrid + blockIdx.x] = s3;
+  if (t == 0) a.part_max[blockIdx.x] = bm;
   for (int w0 = 0; w0 < nwin; w0 += kLbChunk) {
     int sl[kLbChunk];
     bool on[kLbChunk];
@@ -108,28 +150,45 @@ __device__ void lbfgs_dots(const LbfgsArgs& a) {
     double v[5 * kLbChunk];
 #pragma unroll
     for (int q = 0; q < 5 * kLbChunk; ++q) v[q] = 0.0;
-    for (int64_t i = lo + t; i < hi; i += kLbBlock) {
-      const double gi = (double)g[i], si = (double)sh[i], yi = (double)yh[i];
+    const TR* __restrict__ Sk[kLbChunk];
+    const TR* __restrict__ Yk[kLbChunk];
 #pragma unroll
-      for (int c = 0; c < kLbChunk; ++c) {
-        if (on[c]) {
-          const double sk = (double)S[(int64_t)sl[c] * n + i], yk = (double)Y[(int64_t)sl[c] * n + i];
-          v[5 * c + 0] = fma(sk, yi, v[5 * c + 0]);
-          v[5 * c + 1] = fma(yk, si, v[5 * c + 1]);
-          v[5 * c + 2] = fma(yk, yi, v[5 * c + 2]);
-          v[5 * c + 3] = fma(sk, gi, v[5 * c + 3]);
-          v[5 * c + 4] = fma(yk, gi, v[5 * c + 4]);
+    for (int c = 0; c < kLbChunk; ++c) {
+      Sk[c] = S + (int64_t)sl[c] * n;
+      Yk[c] = Y + (int64_t)sl[c] * n;
+    }
+    for_range(lo + t, hi, [&](auto len, int64_t i) {
+      constexpr int L = decltype(len)::value;
+      TR gi[L], si[L], yi[L], sk[L][kLbChunk], yk[L][kLbChunk];
+#pragma unroll
+      for (int u = 0; u < L; ++u) {
+        const int64_t k = i + u * kLbBlock;
+        gi[u] = g[k];
+        si[u] = sh[k];
+        yi[u] = yh[k];
+#pragma unroll
+        for (int c = 0; c < kLbChunk; ++c) {
+          sk[u][c] = on[c] ? Sk[c][k] : TR(0);
+          yk[u][c] = on[c] ? Yk[c][k] : TR(0);
         }
       }
-    }
-    block_sum<5 * kLbChunk, kLbBlock>(v);
-    if (t == 0) {
 #pragma unroll
-      for (int c = 0; c < kLbChunk; ++c)
-        if (on[c])
+      for (int u = 0; u < L; ++u)
 #pragma unroll
-          for (int q = 0; q < 5; ++q)
-            a.part[(size_t)(3 + 5 * sl[c] + q) * kMaxGrid + blockIdx.x] = v[5 * c + q];
+        for (int c = 0; c < kLbChunk; ++c) {
+          if (!on[c]) continue;
+          const double s1 = (double)sk[u][c], y1 = (double)yk[u][c];
+          v[5 * c + 0] = fma(s1, (double)yi[u], v[5 * c + 0]);
+          v[5 * c + 1] = fma(y1, (double)si[u], v[5 * c + 1]);
+          v[5 * c + 2] = fma(y1, (double)yi[u], v[5 * c + 2]);
+          v[5 * c + 3] = fma(s1, (double)gi[u], v[5 * c + 3]);
+          v[5 * c + 4] = fma(y1, (double)gi[u], v[5 * c + 4]);
+        }
+    });
+    const double sk = block_sum_k<5 * kLbChunk>(v);
+    if (t < 5 * kLbChunk && w0 + t / 5 < nwin) {
+      const int w = w0 + t / 5, slot = w == 0 ? h : ring_newest(*mp, a.mem, w - 1);
+      a.part[(size_t)(3 + 5 * slot + t % 5) * kMaxGrid + blockIdx.x] = sk;
     }
   }
 }
@@ -154,22 +213,26 @@ __device__ void lbfgs_scalar(const LbfgsArgs& a) {
   const int K = 3 + 5 * Rm;
   const LbfgsMeta* mp = a.meta_prev;
   LbfgsMeta* m = a.meta;
-  // every sum over the producer blocks: wavefront wv takes sums wv, wv + 4, ..., four at a time
+  // every sum over the producer blocks (at most 4 per lane): wavefront wv takes sums wv,
+  // wv + kLbWaves, ..., four at a time, their loads in flight together
   constexpr int kB = 4;
-  for (int k0 = wv; k0 < K; k0 += 4 * kB) {
-    double acc[kB];
+  for (int k0 = wv; k0 < K; k0 += kLbWaves * kB) {
+    double part[kB][4], acc[kB];
 #pragma unroll
-    for (int q = 0; q < kB; ++q) {
-      const int k = k0 + 4 * q;
-      acc[q] = 0.0;
-      if (k < K)
-        for (unsigned b = lane; b < a.nprod; b += kWave) acc[q] += a.part[(size_t)k * kMaxGrid + b];
-    }
+    for (int q = 0; q < kB; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = min(k0 + kLbWaves * q, K - 1);
+        const unsigned b = lane + j * kWave;
+        part[q][j] = b < a.nprod ? a.part[(size_t)k * kMaxGrid + b] : 0.0;
+      }
+#pragma unroll
+    for (int q = 0; q < kB; ++q) acc[q] = ((part[q][0] + part[q][1]) + part[q][2]) + part[q][3];
     wave_sums<kB>(acc);
     if (lane == 0)
 #pragma unroll
       for (int q = 0; q < kB; ++q)
-        if (k0 + 4 * q < K) sums[k0 + 4 * q] = acc[q];
+        if (k0 + kLbWaves * q < K) sums[k0 + kLbWaves * q] = acc[q];
   }
   double gm = 0.0;
   for (unsigned b = t; b < a.nprod; b += kLbBlock) gm = fmax(gm, a.part_max[b]);
@@ -281,7 +344,22 @@ __device__ void lbfgs_combine(const LbfgsArgs& a) {
   const int64_t stride = (int64_t)gridDim.x * kLbBlock;
   for (int64_t i = (int64_t)blockIdx.x * kLbBlock + t; i < n; i += stride) {
     TR d = cg * g[i];
-    for (int j = 0; j < count; ++j) {
+    int j = 0;
+    for (; j + 4 <= count; j += 4) {   // the loads of four pairs in flight together
+      TR yv[4], sv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t o = (int64_t)sls[j + u] * n + i;
+        yv[u] = Y[o];
+        sv[u] = S[o];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        d = fmad((TR)cfy[j + u], yv[u], d);
+        d = fmad((TR)cfs[j + u], sv[u], d);
+      }
+    }
+    for (; j < count; ++j) {
       const int64_t o = (int64_t)sls[j] * n + i;
       d = fmad((TR)cfy[j], Y[o], d);
       d = fmad((TR)cfs[j], S[o], d);
@@ -303,14 +381,16 @@ __global__ __launch_bounds__(kLbBlock) void k_lbfgs(LbfgsArgs a) {
 
 }  // namespace
 
+// The combination: an element per thread up to 1024 workgroups.
 unsigned lbfgs_grid(int64_t n) {
-  const int64_t per = (int64_t)kLbBlock * 8;
-  const int64_t b = (n + per - 1) / per;
+  const int64_t b = (n + kLbBlock - 1) / kLbBlock;
   return (unsigned)(b < 1 ? 1 : (b > 1024 ? 1024 : b));
 }
 
+// The inner products: two elements per thread up to one workgroup per CU (kLbScalar reads four
+// workgroups' sums per lane).
 unsigned lbfgs_dots_grid(int64_t n) {
-  const int64_t per = (int64_t)kLbBlock * 8;
+  const int64_t per = (int64_t)kLbBlock * 2;
   const int64_t b = (n + per - 1) / per;
   return (unsigned)(b < 1 ? 1 : (b > 256 ? 256 : b));
 }
