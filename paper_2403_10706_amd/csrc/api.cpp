@@ -456,12 +456,9 @@ hipError_t run_level_lbfgs(const CorrectWs& w, const Geom& g, const void* Ip, co
     a.mem = mem;
     a.pair = it > 0 ? 1 : 0;
     // the new pair needs gamma of the previous step: before the state is reset below
+    a.lf = LossFinalArgs{k.slot(kPartLoss), Llg.grid, g.vol, o->alpha, o->beta, k.st, nullptr, rec, 1};
     a.phase = kLbDots;
     if ((e = launch_lbfgs(a, real, s)) != hipSuccess) return e;
-    if ((e = launch_loss_final(LossFinalArgs{k.slot(kPartLoss), Llg.grid, g.vol, o->alpha,
-                                             o->beta, k.st, nullptr, rec, 1},
-                               s)) != hipSuccess)
-      return e;
     a.phase = kLbScalar;
     if ((e = launch_lbfgs(a, real, s)) != hipSuccess) return e;
     a.phase = kLbCombine;

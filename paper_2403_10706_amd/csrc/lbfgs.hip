@@ -11,7 +11,8 @@
 //   kLbDots: the new pair s = gamma x, y = g - g_old into the free ring slot (steps >= 1), and
 //     the block sums of s.y, y.y, s.s and, for every pair of the window (the new one and those
 //     kept so far), s_k.y, y_k.s, y_k.y, s_k.g, y_k.g; the block maxima of |g|
-//   kLbScalar (one block): the sums; the admission of the pair (s^T y > 1e-10 |s| |y|), the Gram
+//   kLbScalar (one block): the objective from loss_grad's block sums, which also resets the line
+//     search state (so after kLbDots has read gamma); the sums; the admission of the pair (s^T y > 1e-10 |s| |y|), the Gram
 //     entries of its slot, the two loops on scalars, cg, cs, cy, and the pair count and H0 scale
 //     in the state (H0 = s^T y / y^T y of the newest pair, 1 / max|g| without pairs)
 //   kLbCombine: d from the coefficients.
@@ -201,6 +202,8 @@ __device__ __forceinline__ double lane_sum(double v) {
 }
 
 __device__ void lbfgs_scalar(const LbfgsArgs& a) {
+  static_assert(kLbBlock == kReduceBlock, "the objective's reduction");
+  if (finalize_loss(a.lf, true)) return;   // the barrier is violated: the level stops
   constexpr int R = kLbfgsMaxMem + 1;
   __shared__ double sums[3 + 5 * R];
   __shared__ double gsy[kLbfgsMaxMem][kLbfgsMaxMem], gyy[kLbfgsMaxMem][kLbfgsMaxMem];

@@ -366,6 +366,7 @@ struct LbfgsArgs {
   State* st;
   int32_t mem;                // pairs kept at most
   int32_t phase;
+  LossFinalArgs lf;           // kLbScalar: J, D, S, P of the current iterate
   int32_t pair;               // this step forms a pair (every step but the first of a level)
   unsigned nblk;              // set by the launcher
 };
