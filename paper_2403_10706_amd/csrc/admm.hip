@@ -220,6 +220,9 @@ __global__ __launch_bounds__(kBpBlock) void k_block_pcg_stats(BlockPcgArgs a) {
 // wavefront read few distinct table entries (multicast) and lines in distinct banks.  Element,
 // line and work-item indices split by multiply-shift divisions in 32 bits (a field has at most
 // 2^28 nodes).
+// Frequencies l that a line's work items sum: up to n / 4 for even n, up to n / 2 for odd n.
+__host__ __device__ constexpr int dht_items(int n) { return n % 2 == 0 ? n / 4 + 1 : n / 2 + 1; }
+
 template <typename TR>
 __global__ __launch_bounds__(kDhtBlock) void k_dht(DhtArgs a) {
   if (load_flag(&a.st->gn_stop)) return;
@@ -313,43 +316,74 @@ __global__ __launch_bounds__(kDhtBlock) void k_dht(DhtArgs a) {
       }
     };
     // H x at frequency l is C + S and at n - l it is C - S, with C and S the sums of x_j times
-    // cos and sin of 2 pi j l / n: one pass over j serves both frequencies, and the index j l mod n
-    // is shared by the kDhtLines lines of a work item
-    const int nh = n / 2 + 1;
+    // cos and sin of 2 pi j l / n.  cos is even and sin odd in j -> n - j, so C takes the sums
+    // x_j + x_(n-j) and S the differences, both over j <= n / 2 only; they replace the pair in LDS.
+    // For even n the even and the odd j are summed apart: cos and sin at n / 2 - l are (-1)^j and
+    // -(-1)^j times those at l, so C_even -+ C_odd and S_odd -+ S_even give n / 2 - l and n / 2 + l
+    // as well: a quarter of the frequencies, half of the terms.
+    const int mh = (n - 1) / 2;   // pairs (j, n - j)
+    const bool quad = n % 2 == 0;
+    for (uint32_t e = threadIdx.x; e < (uint32_t)(lpb * mh); e += kDhtBlock) {
+      const int j = 1 + (int)fdiv(e, a.by_lpb), li = (int)e - (j - 1) * lpb;
+      if (li >= nl) continue;
+      TR* x = xs + li * ns;
+      const TR x1 = x[j], x2 = x[n - j];
+      x[j] = x1 + x2;
+      x[n - j] = x1 - x2;
+    }
+    __syncthreads();
+    const int nh = dht_items(n);                         // frequencies with work of their own
     const int ngr = (lpb + kDhtLines - 1) / kDhtLines;   // line pairs of a full tile
     const int ngl = (nl + kDhtLines - 1) / kDhtLines;    // of this tile
     for (uint32_t e = threadIdx.x; e < (uint32_t)(ngr * nh); e += kDhtBlock) {
       const int l = (int)fdiv(e, a.by_ngr), gi = (int)e - l * ngr;
       if (gi >= ngl) continue;
       const TR* xl[kDhtLines];
-      TR C[kDhtLines], S[kDhtLines];
+      TR Ce[kDhtLines], Co[kDhtLines], Se[kDhtLines], So[kDhtLines];
 #pragma unroll
       for (int q = 0; q < kDhtLines; ++q) {
         const int li = gi * kDhtLines + q;
         xl[q] = xs + (li < nl ? li : nl - 1) * ns;   // past the tile: a valid line, not stored
-        C[q] = S[q] = TR(0);
+        Ce[q] = xl[q][0] * cs[0];
+        Co[q] = Se[q] = So[q] = TR(0);
       }
-      int idx = 0;
-      for (int j = 0; j < n; ++j) {
+      int idx = 0;   // j l mod n
+      auto term = [&](int j, TR (&C)[kDhtLines], TR (&S)[kDhtLines]) {
+        idx += l;
+        if (idx >= n) idx -= n;
         const TR c = cs[2 * idx], sn = cs[2 * idx + 1];
 #pragma unroll
         for (int q = 0; q < kDhtLines; ++q) {
-          const TR x = xl[q][j];
-          C[q] = fma(x, c, C[q]);
-          S[q] = fma(x, sn, S[q]);
+          C[q] = fma(xl[q][j], c, C[q]);
+          S[q] = fma(xl[q][n - j], sn, S[q]);
         }
-        idx += l;
-        if (idx >= n) idx -= n;
+      };
+      int j = 1;
+      for (; j < mh; j += 2) {
+        term(j, Co, So);
+        term(j + 1, Ce, Se);
+      }
+      if (j <= mh) term(j, Co, So);
+      if (quad) {   // j = n / 2: cos is (-1)^l, sin 0
+        const TR c = l % 2 ? -cs[0] : cs[0];
+#pragma unroll
+        for (int q = 0; q < kDhtLines; ++q) {
+          TR& C = n % 4 == 0 ? Ce[q] : Co[q];
+          C = fma(xl[q][n / 2], c, C);
+        }
       }
 #pragma unroll
       for (int q = 0; q < kDhtLines; ++q) {
         const int li = gi * kDhtLines + q;
         if (li >= nl) continue;
         const double lo = scale ? other_term(li) : 0.0;
-        const int nout = (l > 0 && 2 * l != n) ? 2 : 1;
-        for (int o = 0; o < nout; ++o) {
-          const int lout = o == 0 ? l : n - l;
-          emit(li, lout, o == 0 ? C[q] + S[q] : C[q] - S[q], lo);
+        const TR C = Ce[q] + Co[q], S = Se[q] + So[q];
+        emit(li, l, C + S, lo);
+        if (l > 0) emit(li, n - l, C - S, lo);
+        if (quad && 4 * l != n) {
+          const TR C2 = Ce[q] - Co[q], S2 = So[q] - Se[q];
+          emit(li, n / 2 - l, C2 + S2, lo);
+          if (l > 0) emit(li, n / 2 + l, C2 - S2, lo);
         }
       }
     }
@@ -482,7 +516,20 @@ hipError_t launch_block_pcg(const BlockPcgArgs& a0, DType real, hipStream_t s) {
 unsigned dht_grid(const int32_t n[3], int axis, int* lines_per_block) {
   const int u0 = axis == 0 ? 1 : 0, u1 = axis == 2 ? 1 : 2;
   const int64_t nlines = (int64_t)n[u0] * n[u1];
-  const int lpb = kDhtElems / (n[axis] | 1) < 1 ? 1 : kDhtElems / (n[axis] | 1);
+  // lines per workgroup: of those that fit, the number whose work items fill the workgroup's rounds
+  // best (144 nodes: 12 lines, 222 items for 256 threads, where 14 would leave 3 for a second round)
+  const int nh = dht_items(n[axis]);
+  const int most = kDhtElems / (n[axis] | 1) / kDhtLines;
+  int lpb = 1;
+  double best = 0.0;
+  for (int p = 1; p <= most; ++p) {
+    const int items = p * nh, rounds = (items + kDhtBlock - 1) / kDhtBlock;
+    const double fill = (double)items / (rounds * kDhtBlock);
+    if (fill >= best) {
+      best = fill;
+      lpb = p * kDhtLines;
+    }
+  }
   *lines_per_block = lpb;
   const int64_t b = (nlines + lpb - 1) / lpb;
   return (unsigned)(b > kMaxGrid ? kMaxGrid : b);
