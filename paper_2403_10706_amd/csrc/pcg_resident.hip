@@ -459,7 +459,7 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     if (t < a.units) {
       const u64 t0 = wall_clock64();
       while ((uint32_t)(word_get(a.sync + t) >> 32) != tag0) {
-        if (wall_clock64() - t0 > kArriveTicks) {
+        if (wall_clock64() - t0 > kArriveTicks + a.patience) {
           ok = false;
           break;
         }
@@ -725,7 +725,7 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
 }
 
 template <typename TR, int NPT, int XL, int KEEP, int XN, int S>
-__global__ __launch_bounds__(kResBlock, 2) void k_pcg_resident(ResBatch b) {
+__global__ __launch_bounds__(kResBlock, XL <= 2 ? 4 : 2) void k_pcg_resident(ResBatch b) {
   int p = 0;
   while (p + 1 < b.n && (int)blockIdx.x >= b.start[p + 1]) ++p;
   const ResArgs& a = b.v[p];
@@ -847,8 +847,10 @@ hipError_t launch_pcg_resident_one(const ResArgs& a, const ResPlan& L, DType rea
 }
 
 hipError_t launch_pcg_resident(const ResBatch& b, DType real, int tier, size_t lds, hipStream_t s) {
-  if (b.n < 1 || b.n > kMaxResVolumes || b.start[b.n] > kMaxResUnits || lds > kMaxResLds)
-    return hipErrorInvalidValue;
+  if (b.n < 1 || b.n > kMaxResVolumes || lds > kMaxResLds) return hipErrorInvalidValue;
+  for (int p = 0; p < b.n; ++p)
+    if (b.v[p].units > kMaxResUnits || b.start[p + 1] - b.start[p] != b.v[p].units)
+      return hipErrorInvalidValue;
   const unsigned grid = (unsigned)b.start[b.n];
   int64_t cells = 0, nodes = 0;
   for (int p = 0; p < b.n; ++p) {

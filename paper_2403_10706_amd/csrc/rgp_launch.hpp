@@ -213,6 +213,7 @@ struct ResArgs {
   double* relres_out;         // nullable
   LossFinalArgs lf;           // gn_mode: J, D, S, P of the current iterate
   int32_t gn_mode, maxit;
+  uint32_t patience;          // added to the wait for arrivals: volumes before this one may be solved first
   uint32_t tag;               // first tag of this launch (tag .. tag + maxit are its own)
   int32_t no, na, nb, role, P, T, XL, noc, units;
   uint32_t nnode, ncell;
