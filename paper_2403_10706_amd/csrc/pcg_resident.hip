@@ -21,13 +21,14 @@
 // against it: the others leave and the first one solves the volume alone from memory.
 //
 // What bounds it (rgp_pcg_solve with 20 iterations, us per iteration, stepped against resident):
-//   25x25x17 FP32 14.5 / 5.1   72x84x56 17.9 / 7.0   144x168x111 33.9 / 13.9   200x200x132 54 / 38
-//   32x32x24 FP64 19 / 5.4     90x90x90 FP64 31 / 12.4
+//   25x25x17 FP32 14.5 / 5.1   72x84x56 17.9 / 7.0   144x168x111 33.9 / 14.1   200x200x132 54 / 28
+//   32x32x24 FP64 19 / 5.5     90x90x90 FP64 31 / 12.2
 // Small volumes: two exchanges per iteration (outer p and sums), about 1 us of latency each, and
-// the workgroup barriers between.  144x168x111: of 12.6 us, 3.4 wait for the outer p (8 MB of words
-// each way), 1.9 for the sums, 2.3 + 1.6 are the stencil and its reduction, 2.9 the update.  Above
-// that d and the couplings no longer fit the registers and are read again from the L2 (200x200x132:
-// stencil 9.6, update 12 us of 35).
+// the workgroup barriers between.  144x168x111: of 12.7 us, 3.3 wait for the outer p (8 MB of words
+// each way), 2 for the sums, 2.3 + 1.6 are the stencil and its reduction (FP64 issue), 2.8 the update.
+// Above that d and the couplings no longer fit the registers and are read again from the L2, a group
+// of planes ahead of their use (200x200x132: stencil 8 and update 7 of 25 us; with a position's
+// planes read together, right before their use, 9.6 and 12 of 35).
 //
 // Arithmetic: node for node that of the stepped form (pcg.hip), with the block sums formed over
 // this form's own partition.
@@ -509,8 +510,11 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     lds[q * S + lc[i]] = p;
     if (has(i, kEdge) || q == 0 || q == np - 1) value_put(words, node(q, i), p, tag);
   };
-  // planes in the order in which an update takes them: the outer ones first
-  auto nth = [](int k) -> int { return k == 0 ? 0 : (k == 1 ? XL - 1 : k - 1); };
+  // planes in the order in which an update takes them: the outer ones first (in their order where
+  // the diagonal is read again, group by group)
+  auto nth = [](int k) -> int {
+    return !KD && !KR ? k : (k == 0 ? 0 : (k == 1 ? XL - 1 : k - 1));
+  };
   {
     u64* words = a.words + (size_t)((tag0 + 1u) & 1u) * wstride;
 #pragma unroll
@@ -526,6 +530,26 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
       }
   }
 
+  // What is not kept in registers is read again group by group of planes, one group ahead of its
+  // use (a group takes longer than a read from the L2).  Every read is unconditional, so that none
+  // is moved to its use.
+  struct Stream {
+    TR d[kResGroup], o[kResGroup], l[kResGroup];
+  };
+  auto fetch = [&](int i, int g, bool couplings) -> Stream {
+    Stream f{};
+#pragma unroll
+    for (int j = 0; j < kResGroup; ++j) {
+      const int q = min(g * kResGroup + j, np - 1);
+      if (!KD) f.d[j] = bld<TR>(rD, node(q, i) * kSz);
+      if (KO || !couplings) continue;
+      f.o[j] = bld<TR>(rO, node(q, i) * kSz);
+      f.l[j] = lower(q, i);
+    }
+    return f;
+  };
+  constexpr bool kStream = !KD || !KO;
+
   double bn = 0.0, rel = 0.0;
   int its = 0;
   bool lost = false;
@@ -534,6 +558,7 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     const uint32_t tag = tag0 + (uint32_t)it;
     opaque();
     const u64* words = a.words + (size_t)(tag & 1u) * wstride;
+    Stream now = fetch(0, 0, true);
     // p at the planes before and after the unit and in the rows before and after its tile, all in
     // flight together; p after the unit and the rows go to LDS (the former to slots that only this
     // thread reads)
@@ -580,18 +605,6 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
-      // what is not kept in registers: all planes in flight together
-      TR so[KO ? 1 : XL], sl[KO || ROLE == 0 ? 1 : XL];
-      TR sd[KD ? 1 : XL];
-      if (!KO || !KD) {
-#pragma unroll
-        for (int q = 0; q < XL; ++q) {
-          if (!KD) sd[KD ? 0 : q] = bld<TR>(rD, node(min(q, np - 1), i) * kSz);
-          if (KO) continue;
-          so[KO ? 0 : q] = bld<TR>(rO, node(min(q, np - 1), i) * kSz);
-          if (ROLE != 0) sl[KO || ROLE == 0 ? 0 : q] = lower(min(q, np - 1), i);
-        }
-      }
       const TR* cc = lds + lc[i];
       const TR* cam = lds + (has(i, kNoLo) ? S - 1 : lc[i] - nb);
       const TR* cap = lds + (has(i, kNoHi) ? S - 1 : lc[i] + nb);
@@ -600,7 +613,13 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
       TR pom = pm[i], pk = cc[0], ol = om[i];
 #pragma unroll
       for (int q0 = 0; q0 < XL; q0 += kResGroup) {
-        if (q0 >= np) continue;
+        if (!kStream && q0 >= np) continue;
+        const Stream f = now;
+        if (kStream) {
+          const bool more = q0 + kResGroup < XL;
+          if (more || i + 1 < NPT) now = fetch(more ? i : i + 1, more ? q0 / kResGroup + 1 : 0, true);
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int q = q0; q < q0 + kResGroup && q < XL; ++q) {
           const TR pop = cc[(q + 1) * S], pam = cam[q * S], pap = cap[q * S];
@@ -610,9 +629,9 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
           if (KR) keep_single(rd[KR ? q : 0][i]);
           if (KO) keep_single(oc[KO ? q : 0][i]);
           if (KO && ROLE != 0) keep_single(ob[KO && ROLE != 0 ? q : 0][i]);
-          const TR ou = KO ? oc[KO ? q : 0][i] : so[KO ? 0 : q];
-          if (ROLE != 0) ol = KO ? ob[KO && ROLE != 0 ? q : 0][i] : sl[KO || ROLE == 0 ? 0 : q];
-          const TR dk = KD ? d[KD ? q : 0][i] : sd[KD ? 0 : q];
+          const TR ou = KO ? oc[KO ? q : 0][i] : f.o[q - q0];
+          if (ROLE != 0) ol = KO ? ob[KO && ROLE != 0 ? q : 0][i] : f.l[q - q0];
+          const TR dk = KD ? d[KD ? q : 0][i] : f.d[q - q0];
           TR wv = res_stencil<TR>(ROLE, dk, pk, pom, pop, pam, pap, pbm, pbp, ol, ou, c_o, c_a,
                                   c_b);
           wv = has(i, kOwn) && q < np ? wv : TR(0);
@@ -634,6 +653,7 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
       word_put(mine, tagged(tag, (uint32_t)__double2loint(s)));
       word_put(mine + 1, tagged(tag, (uint32_t)__double2hiint(s)));
     }
+    if (!KD && !KR) now = fetch(NPT - 1, 0, false);   // the update's, under the wait
     double us;
     const bool got = a.units <= 64 ? sums_get<2>(part, a.units, tag, us)
                                    : (a.units <= 128 ? sums_get<4>(part, a.units, tag, us)
@@ -663,15 +683,14 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     opaque();
 #pragma unroll
     for (int i = NPT - 1; i >= 0; --i) {
-      if (!has(i, kOwn)) continue;
-      TR sd[KD || KR ? 1 : XL];
-      if (!KD && !KR) {
-#pragma unroll
-        for (int q = 0; q < XL; ++q)
-          sd[KD || KR ? 0 : q] = bld<TR>(rD, node(min(q, np - 1), i) * kSz);
-      }
 #pragma unroll
       for (int k0 = 0; k0 < XL; k0 += kResGroup) {
+        const Stream f = now;
+        if (!KD && !KR) {
+          const bool more = k0 + kResGroup < XL;
+          if (more || i > 0) now = fetch(more ? i : i - 1, more ? k0 / kResGroup + 1 : 0, false);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         TR po[kResGroup], xv[kResGroup];
 #pragma unroll
         for (int j = 0; j < kResGroup && k0 + j < XL; ++j) {
@@ -691,9 +710,9 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
           const TR rv = fmad(-al, w[q][i], r[q][i]);
           r[q][i] = rv;
           const TR inv = KR ? rd[KR ? q : 0][i]
-                            : TR(1) / (KD ? d[KD ? q : 0][i] : sd[KD || KR ? 0 : q]);
+                            : TR(1) / (KD ? d[KD ? q : 0][i] : f.d[j]);
           const TR pn = fmad(be, po[j], rv * inv);
-          if (q < np && !fin) put_p(q, i, pn, next, tag + 1u);
+          if (q < np && !fin && has(i, kOwn)) put_p(q, i, pn, next, tag + 1u);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -756,7 +775,7 @@ namespace {
 // The variants, in the order in which the planner tries them.  A thread has 256 registers; r and w
 // of its nodes take two each, everything kept seven.  Up to 8 planes (16 nodes) all of it fits;
 // at 12 planes x moves to LDS (without that 40 registers spilled and the update took 5.4 instead
-// of 1.9 us), at 16 the couplings and then d are read again.  Units of at least 2 planes: with one
+// of 1.9 us), at 16 the couplings and, with a third position per thread, d are read again.  Units of at least 2 planes: with one
 // the sums come from twice the workgroups.
 constexpr ResTier kTiersF32[] = {{2, 2, kKeepAll, 0, 1537},  {2, 4, kKeepAll, 0, 1537},
                                  {2, 8, kKeepAll, 0, 1537},  {2, 12, kKeepAll, 2, 1537},
