@@ -65,7 +65,7 @@ class PyramidObjective(torch.autograd.Function):
                 hl = tuple(2.0 * x for x in hl)
             jdsp, _, _, _ = rgp.loss_grad(P, M, b, pe, hl, alpha, beta, want_grad=False,
                                           want_hess=False)
-            Jl = jdsp[0] * weights[l]
+            Jl = jdsp[0] if weights[l] == 1.0 else jdsp[0] * weights[l]
             J = Jl if J is None else J + Jl
         ctx.save_for_backward(I_plus, I_minus, *fields)
         ctx.cfg = (pe, tuple(h), alpha, beta, tuple(weights))
@@ -84,12 +84,14 @@ class PyramidObjective(torch.autograd.Function):
                 P, M = rgp.restrict_image(P, b.dtype), rgp.restrict_image(M, b.dtype)
                 hl = tuple(2.0 * x for x in hl)
             levels.append((P, M, hl))
+        # in the fields' type; weights of 1 multiply nothing (here and below)
+        s = gJ.to(fields[0].dtype)
         g_fields = []
         for l, (b, (P, M, hl)) in enumerate(zip(fields, levels)):
             if need_b[l]:
                 _, g, _, _ = rgp.loss_grad(P, M, b, pe, hl, alpha, beta, want_grad=True,
                                            want_hess=False)
-                g_fields.append(g * (gJ.to(g.dtype) * weights[l]))
+                g_fields.append(g * (s if weights[l] == 1.0 else s * weights[l]))
             else:
                 g_fields.append(None)
         g_p = g_m = None
@@ -105,7 +107,6 @@ class PyramidObjective(torch.autograd.Function):
                     rgp.restrict_image_adjoint(acc_p, tuple(P.shape), out=gp, accumulate=True)
                     rgp.restrict_image_adjoint(acc_m, tuple(M.shape), out=gm, accumulate=True)
                 acc_p, acc_m = gp, gm
-            s = gJ.to(acc_p.dtype)
             g_p = (acc_p * s).to(I_plus.dtype) if need_p else None
             g_m = (acc_m * s).to(I_minus.dtype) if need_m else None
         return (g_p, g_m, None, None, None, None, None, *g_fields)
