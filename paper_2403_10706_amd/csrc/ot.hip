@@ -178,8 +178,14 @@ __device__ __forceinline__ unsigned xcd_tile(unsigned b, unsigned G) {
 //      Then C- replaces C+ in the same LDS array and the own C+ values are the queries.  One
 //      FP64 array per column keeps a full-resolution grid resident in a single round.
 //   3. Guard: the slope of the first own cell takes the previous segment's last node through LDS.
+// Bound by the latency of the searches' dependent LDS reads, so by the wavefronts in flight: of C+,
+// C- and the inverses only two are held in registers at a time (the third is in LDS), and the images
+// and the result are addressed by 32-bit offsets.  That takes 16 cells per segment from 3 to 4
+// wavefronts per SIMD (124 registers) and 8 cells from 4 to 6 (80).  At 200x200x132 (columns of 200,
+// 1650 tiles): 74 us in three rounds of 768 tiles before, 52 us in two of 1024; 250x180x110 BF16
+// 59 -> 49 us, 144x168x111 (999 tiles, one round before and after) 33 -> 31 us.
 template <typename TI, typename TR, int NC, int LMAX>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 12 ? 4 : LMAX <= 16 ? 3 : 1))) void k_ot(OtArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 8 ? 6 : LMAX <= 16 ? 4 : 1))) void k_ot(OtArgs a) {
   constexpr int NSEG = kBlock / NC;
   constexpr int NW = kBlock / kWave;
   static_assert(NC >= 1 && NC <= kWave && kWave % NC == 0, "columns per tile");
@@ -202,17 +208,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
   const int j0 = min(mp, seg * L), n = min(mp, j0 + L) - j0;
 
   // 1. loads of the own cells (all in flight together), then the block extrema of the shift kernel
-  const TI* __restrict__ srcp =
-      static_cast<const TI*>(a.Ip) + ((int64_t)ix * g.cxs + (int64_t)iy * g.cys + (int64_t)j0 * g.cps);
-  const TI* __restrict__ srcm =
-      static_cast<const TI*>(a.Im) + ((int64_t)ix * g.cxs + (int64_t)iy * g.cys + (int64_t)j0 * g.cps);
-  TI vp[LMAX], vm[LMAX];
+  const BRes rp = bres(a.Ip, (uint32_t)g.ncell * (uint32_t)sizeof(TI));
+  const BRes rm = bres(a.Im, (uint32_t)g.ncell * (uint32_t)sizeof(TI));
+  const uint32_t cps = (uint32_t)g.cps * (uint32_t)sizeof(TI);
+  const uint32_t off0 = (ix * (uint32_t)g.cxs + iy * (uint32_t)g.cys + (uint32_t)j0 * (uint32_t)g.cps) *
+                        (uint32_t)sizeof(TI);
+  typedef typename std::conditional<std::is_same<TI, double>::value, double, float>::type TV;
+  TV vp[LMAX], vm[LMAX];
 #pragma unroll
   for (int u = 0; u < LMAX; ++u) {
-    if (u < n) {
-      vp[u] = srcp[(int64_t)u * g.cps];
-      vm[u] = srcm[(int64_t)u * g.cps];
-    }
+    const uint32_t off = u < n ? off0 + (uint32_t)u * cps : kNullOff;
+    vp[u] = bld_img<TI, TV>(rp, off);
+    vm[u] = bld_img<TI, TV>(rm, off);
   }
   double lo = inf_d(), hi = 0.0, bad = 0.0;
   for (unsigned b = tid; b < a.shift_nprod; b += kBlock) {
@@ -227,10 +234,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
   double accp = 0.0, accm = 0.0;
 #pragma unroll
   for (int u = 0; u < LMAX; ++u) {
-    if (u < n) {
-      accp += to_real(vp[u], double());
-      accm += to_real(vm[u], double());
-    }
+    accp += (double)vp[u];   // 0 beyond the segment
+    accm += (double)vm[u];
     Cp[u] = accp;
     Cm[u] = accm;
   }
@@ -305,9 +310,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
   __syncthreads();
   if (massok && n > 0) invert_run<NC, LMAX, true>(C, mp, Cm, n, 0.0, bv);
   __syncthreads();
+  // each node's C- replaces its C+, which comes back as a query: neither need be held in registers
+  // while the other is searched (the empty asm keeps the compiler from holding C+ all the same)
+  asm volatile("" ::: "memory");
 #pragma unroll
-  for (int u = 0; u < LMAX; ++u)
-    if (u < n) C[(j0 + 1 + u) * NC] = Cm[u];
+  for (int u = 0; u < LMAX; ++u) {
+    Cp[u] = 0.0;
+    if (u < n) {
+      Cp[u] = C[(j0 + 1 + u) * NC];
+      C[(j0 + 1 + u) * NC] = Cm[u];
+    }
+  }
   __syncthreads();
   const double hp = g.hp;
   if (massok && n > 0) invert_run<NC, LMAX, false>(C, mp, Cp, n, 0.25 * hp, bv);
@@ -363,13 +376,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
     }
   }
 
-  if (colok) {
-    TR* __restrict__ out = static_cast<TR*>(a.b0) + ((int64_t)ix * g.nxs + (int64_t)iy * g.nys);
-    if (seg == 0) out[0] = (TR)0.0;
+  const BRes ro = bres(a.b0, (uint32_t)g.nnode * (uint32_t)sizeof(TR));
+  const uint32_t nps = (uint32_t)g.nps * (uint32_t)sizeof(TR);
+  const uint32_t out0 = (ix * (uint32_t)g.nxs + iy * (uint32_t)g.nys + (uint32_t)j0 * (uint32_t)g.nps) *
+                        (uint32_t)sizeof(TR);
+  bst<TR>(ro, seg == 0 && colok ? out0 : kNullOff, (TR)0.0);
 #pragma unroll
-    for (int u = 0; u < LMAX; ++u)
-      if (u < n) out[(int64_t)(j0 + 1 + u) * g.nps] = (TR)bv[u];
-  }
+  for (int u = 0; u < LMAX; ++u)
+    bst<TR>(ro, u < n && colok ? out0 + (uint32_t)(u + 1) * nps : kNullOff, (TR)bv[u]);
 }
 
 // ------------------------------------------------------------------------------------------
