@@ -68,6 +68,12 @@ __device__ __forceinline__ double row_sum(double v) {
   return v;
 }
 
+// Bound by the FP64 issue of the stencil and the three sums (71 us for 20 iterations at 144x168x111,
+// 0.6 TB/s): both sums of the new residual are formed in one pass, and the residual's root and
+// division, a fifth of an iteration's scalar chain, are left out where no residual can stop a column
+// (rtol 0; the reported one is formed once, after the loop).  74 -> 71 us there, 145 -> 138 us at 200x200x132, 36 -> 33 us
+// at 96x120x80.  Four wavefronts per SIMD instead of two (the conversions of d and off repeated in
+// every iteration) spill at 12 nodes per lane: 82 us.
 template <typename TR, int NPL>
 __global__ __launch_bounds__(kBpBlock) void k_block_pcg(BlockPcgArgs a) {
   if (load_flag(&a.st->gn_stop)) return;
@@ -111,7 +117,8 @@ __global__ __launch_bounds__(kBpBlock) void k_block_pcg(BlockPcgArgs a) {
     rz = row_sum(rz);
     bool active = nbv > 0.0;
     int its = 0;
-    double relres = active ? 1.0 : 0.0;
+    const bool any_rhs = active;
+    double rrl = 0.0;   // r.r of the last step
     for (int it = 0; it < a.maxit; ++it) {
       if (!__any(active)) break;
       // q = T p with the neighbours of the run's end nodes from the adjacent lanes
@@ -132,27 +139,24 @@ __global__ __launch_bounds__(kBpBlock) void k_block_pcg(BlockPcgArgs a) {
       pq = row_sum(pq);
       active = active && pq > 0.0;
       const TR al = active ? (TR)(rz / pq) : TR(0);
-      double rr = 0.0;
+      double rr = 0.0, rzn = 0.0;
+      TR z[NPL];
 #pragma unroll
       for (int i = 0; i < NPL; ++i) {
         x[i] = fma(al, p[i], x[i]);
         r[i] = fma(-al, q[i], r[i]);
-        rr = fmad64((double)r[i], (double)r[i], rr);
-      }
-      rr = row_sum(rr);
-      if (active) {
-        ++its;
-        relres = sqrt(rr) / nbv;
-      }
-      const bool cont = active && !(relres < a.rtol);
-      double rzn = 0.0;
-      TR z[NPL];
-#pragma unroll
-      for (int i = 0; i < NPL; ++i) {
         z[i] = r[i] * di[i];
+        rr = fmad64((double)r[i], (double)r[i], rr);
         rzn = fmad64((double)r[i], (double)z[i], rzn);
       }
+      rr = row_sum(rr);
       rzn = row_sum(rzn);
+      if (active) {
+        ++its;
+        rrl = rr;
+      }
+      // the residual is looked at only where it can stop the column
+      const bool cont = active && !(a.rtol > 0.0 && sqrt(rr) / nbv < a.rtol);
       const TR be = cont ? (TR)(rzn / rz) : TR(0);
 #pragma unroll
       for (int i = 0; i < NPL; ++i)
@@ -166,6 +170,7 @@ __global__ __launch_bounds__(kBpBlock) void k_block_pcg(BlockPcgArgs a) {
       if (colok && k <= mp) xg[nb + (int64_t)k * g.nps] = x[i];
     }
     if (colok) {
+      const double relres = !any_rhs ? 0.0 : its > 0 ? sqrt(rrl) / nbv : 1.0;
       mit = fmax(mit, (double)its);
       mrel = fmax(mrel, relres);
     }
