@@ -71,9 +71,9 @@ __device__ __forceinline__ double row_sum(double v) {
 // Bound by the FP64 issue of the stencil and the three sums (71 us for 20 iterations at 144x168x111,
 // 0.6 TB/s): both sums of the new residual are formed in one pass, and the residual's root and
 // division, a fifth of an iteration's scalar chain, are left out where no residual can stop a column
-// (rtol 0; the reported one is formed once, after the loop).  74 -> 71 us there, 145 -> 138 us at 200x200x132, 36 -> 33 us
-// at 96x120x80.  Four wavefronts per SIMD instead of two (the conversions of d and off repeated in
-// every iteration) spill at 12 nodes per lane: 82 us.
+// (rtol 0; the reported one is formed once, after the loop).  74 -> 71 us there, 145 -> 138 us at
+// 200x200x132, 36 -> 33 us at 96x120x80.  Four wavefronts per SIMD instead of two (the conversions
+// of d and off repeated in every iteration) spill at 12 nodes per lane: 82 us.
 template <typename TR, int NPL>
 __global__ __launch_bounds__(kBpBlock) void k_block_pcg(BlockPcgArgs a) {
   if (load_flag(&a.st->gn_stop)) return;
