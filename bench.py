@@ -1195,7 +1195,10 @@ def main():
                     frac=round(s_gbps / HBM_PEAK_GBPS, 4), traffic=traffic,
                     kernel=(f"{'k_pcg_resident' if iters > 1 else 'k_pcg_step'} (finest level, "
                             "144x169x111 nodes, full PCG iterations)"),
-                    bytes_rule="52 B per cell per PCG iteration (HVP + CG vector updates)",
+                    bytes_rule="52 B per cell per PCG iteration (HVP + CG vector updates)"
+                               + ("; the vectors stay on the chip, so this rate may exceed the "
+                                  "memory's peak (moved_bytes: what crosses memory)"
+                                  if iters > 1 else ""),
                     bytes_per_launch=sb * iters, iterations_per_launch=iters,
                     us_per_launch=round(dom["us_mean"] * iters, 3),
                     us_median=round(dom["us_median"] * iters, 3), launches=dom["launches"], grid=dom["grid"],
