@@ -65,7 +65,8 @@ class PyramidObjective(torch.autograd.Function):
                 hl = tuple(2.0 * x for x in hl)
             jdsp, _, _, _ = rgp.loss_grad(P, M, b, pe, hl, alpha, beta, want_grad=False,
                                           want_hess=False)
-            Jl = jdsp[0] if weights[l] == 1.0 else jdsp[0] * weights[l]
+            # (what is returned is a scalar of its own, which a caller may add to, not a view)
+            Jl = jdsp[0] if weights[l] == 1.0 and len(fields) > 1 else jdsp[0] * weights[l]
             J = Jl if J is None else J + Jl
         ctx.save_for_backward(I_plus, I_minus, *fields)
         ctx.cfg = (pe, tuple(h), alpha, beta, tuple(weights))
