@@ -198,7 +198,15 @@ def workspace_size(op: int, shape, pe, h, real_dtype, opts: Optional[SolverOpts]
 
 
 # A call's geometry block and workspace size depend on these values alone, and forming them costs
-# more host time than a launch: the three-level training pass (21 calls) 542 -> 377 us.
+# more host time than a launch.  The keys are plain numbers, converted on each call as make_grid
+# converts them: whatever int() and float() take is accepted, and an array or tensor changed in
+# place is seen.
+def _key(shape, pe, h):
+    if type(shape) is not torch.Size or len(shape) != 3:
+        shape = int(shape[0]), int(shape[1]), int(shape[2])
+    return shape, int(pe), (float(h[0]), float(h[1]), float(h[2]))
+
+
 @functools.lru_cache(maxsize=1024)
 def _grid_of(shape, pe, h) -> Grid:
     return make_grid(shape, pe, h)
@@ -206,12 +214,16 @@ def _grid_of(shape, pe, h) -> Grid:
 
 def _grid(shape, pe, h=(1.0, 1.0, 1.0)) -> Grid:
     """make_grid for a call that only reads it."""
-    return _grid_of(tuple(shape), pe, tuple(h))
+    return _grid_of(*_key(shape, pe, h))
 
 
 @functools.lru_cache(maxsize=1024)
-def _need(op, shape, pe, h, real_dtype) -> int:
+def _need_of(op, shape, pe, h, real_dtype) -> int:
     return workspace_size(op, shape, pe, h, real_dtype)
+
+
+def _need(op, shape, pe, h, real_dtype) -> int:
+    return _need_of(op, *_key(shape, pe, h), real_dtype)
 
 
 class Workspace:
@@ -242,7 +254,7 @@ _WS = Workspace()
 
 def _ws(op, shape, pe, h, real_dtype, device, opts=None, ws=None, stream=None):
     if opts is None:
-        need = _need(op, tuple(shape), pe, tuple(h), real_dtype)
+        need = _need(op, shape, pe, h, real_dtype)
     else:
         need = workspace_size(op, shape, pe, h, real_dtype, opts)
     if ws is None:
@@ -278,7 +290,7 @@ def blur_field(b: torch.Tensor, shape, pe: int, *, out=None, stream=None):
         raise ValueError(f"field shape {tuple(b.shape)} != {field_shape(tuple(shape), pe)}")
     if out is None:
         out = torch.empty_like(b)
-    g = _grid(tuple(shape), pe)
+    g = _grid(shape, pe)
     _check("rgp_blur_field", load().rgp_blur_field(ctypes.byref(g), dtype_code(b.dtype), _ptr(b),
                                                    _ptr(out), _stream_ptr(stream)))
     return out
@@ -340,7 +352,7 @@ def loss_grad_images(I_plus, I_minus, b, pe, h=(1.0, 1.0, 1.0), *, stream=None):
     _dev_check(I_plus, I_minus, b)
     gp = torch.empty(tuple(I_plus.shape), dtype=b.dtype, device=b.device)
     gm = torch.empty_like(gp)
-    g = _grid(tuple(I_plus.shape), pe, h)
+    g = _grid(I_plus.shape, pe, h)
     _check("rgp_loss_grad_images", load().rgp_loss_grad_images(
         ctypes.byref(g), dtype_code(I_plus.dtype), _ptr(I_plus), _ptr(I_minus),
         dtype_code(b.dtype), _ptr(b), _ptr(gp), _ptr(gm), _stream_ptr(stream)))
@@ -359,7 +371,7 @@ def restrict_image(I, real_dtype=None, *, stream=None):
     if real_dtype is None:
         real_dtype = torch.float32 if I.dtype == torch.bfloat16 else I.dtype
     out = torch.empty(coarse_shape(I.shape), dtype=real_dtype, device=I.device)
-    g = _grid(tuple(I.shape), 0)
+    g = _grid(I.shape, 0)
     _check("rgp_restrict_image", load().rgp_restrict_image(
         ctypes.byref(g), dtype_code(I.dtype), _ptr(I), dtype_code(real_dtype), _ptr(out),
         _stream_ptr(stream)))
@@ -424,7 +436,7 @@ def apply_correction(I_plus, I_minus, b, pe, h=(1.0, 1.0, 1.0), *, stream=None):
     _dev_check(I_plus, I_minus, b)
     Tp = torch.empty_like(I_plus)
     Tm = torch.empty_like(I_minus)
-    g = _grid(tuple(I_plus.shape), pe, h)
+    g = _grid(I_plus.shape, pe, h)
     _check("rgp_apply_correction", load().rgp_apply_correction(
         ctypes.byref(g), dtype_code(I_plus.dtype), _ptr(I_plus), _ptr(I_minus),
         dtype_code(b.dtype), _ptr(b), _ptr(Tp), _ptr(Tm), _stream_ptr(stream)))
@@ -517,7 +529,7 @@ def parse_stats(stats: torch.Tensor, levels: int, gn_iters: int):
 
 def correct_into(I_plus, I_minus, pe, opts: Options, b_out, T_plus, T_minus, ws, *, h=(1.0, 1.0, 1.0),
                  stats=None, b_init=None, stream=None):
-    g = _grid(tuple(I_plus.shape), pe, h)
+    g = _grid(I_plus.shape, pe, h)
     copts = opts.to_c(use_b_init=b_init is not None)
     _check("rgp_correct", load().rgp_correct(
         ctypes.byref(g), dtype_code(I_plus.dtype), _ptr(I_plus), _ptr(I_minus),
@@ -527,7 +539,7 @@ def correct_into(I_plus, I_minus, pe, opts: Options, b_out, T_plus, T_minus, ws,
 
 def loss_grad_into(I_plus, I_minus, b, pe, jdsp, grad, hdiag, hoff, ws, *, h=(1.0, 1.0, 1.0),
                    alpha=300.0, beta=1e-4, stream=None):
-    g = _grid(tuple(I_plus.shape), pe, h)
+    g = _grid(I_plus.shape, pe, h)
     _check("rgp_loss_grad", load().rgp_loss_grad(
         ctypes.byref(g), dtype_code(I_plus.dtype), _ptr(I_plus), _ptr(I_minus),
         dtype_code(b.dtype), _ptr(b), float(alpha), float(beta), _ptr(jdsp), _ptr(grad),
@@ -553,7 +565,7 @@ def pcg_solve_into(hdiag, hoff, rhs, x, shape, pe, maxit, ws, *, rtol=0.0, h=(1.
 
 def ot_init_into(I_plus, I_minus, pe, b0, ws, *, h=(1.0, 1.0, 1.0), eps=1e-3, guard=True,
                  n_guarded=None, stream=None):
-    g = _grid(tuple(I_plus.shape), pe, h)
+    g = _grid(I_plus.shape, pe, h)
     _check("rgp_ot_init", load().rgp_ot_init(
         ctypes.byref(g), dtype_code(I_plus.dtype), _ptr(I_plus), _ptr(I_minus),
         dtype_code(b0.dtype), _ptr(b0), float(eps), int(bool(guard)), _ptr(n_guarded), _ptr(ws),
