@@ -49,7 +49,9 @@ typedef enum {
                            the guard off): that level stops with b unchanged */
   RGP_ELINESEARCH = -6, /* no Armijo trial was accepted in some Gauss-Newton step (Sec. 2.3.1):
                            that level stops with b unchanged; later levels still run */
-  RGP_EHIP = -7,        /* a HIP runtime call failed (see rgp_last_hip_error) */
+  RGP_EHIP = -7,        /* a HIP runtime call failed (see rgp_last_hip_error); in a stats header:
+                           a workgroup of a one-launch PCG solve stood still (rgp_pcg_solve), and
+                           that level stopped with b unchanged */
   RGP_EWORKSPACE = -8   /* workspace missing or smaller than rgp_workspace_size() */
 } rgp_status;
 
@@ -246,7 +248,11 @@ rgp_status rgp_gn_hvp(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
  * on another stream of the device, one launch per iteration.  Their block sums are added in
  * different orders, so results agree to rounding; each form by itself is bitwise reproducible.
  * The solves inside rgp_correct, the plans and the batches choose in the same way (a plan holds
- * both forms and chooses at each launch). */
+ * both forms and chooses at each launch).
+ *
+ * The workgroups of the one-launch form wait for each other's values, 2^24 polls (more than 16 s of
+ * running) at most.  When one gives up, *iters_dev is -1, *relres_dev NaN and x NaN where its
+ * workgroup writes it; the call has returned RGP_OK by then. */
 rgp_status rgp_pcg_solve(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
                          const void* hoff, double alpha, const void* rhs, void* x, int32_t maxit,
                          double rtol, int32_t* iters_dev, double* relres_dev, void* ws,

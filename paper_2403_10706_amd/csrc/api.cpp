@@ -39,6 +39,37 @@ int& rgp::batch_march_min() {
   return m;
 }
 
+Geom rgp::make_geom(const int64_t m[3], int pe, const double h[3]) {
+  Geom g{};
+  int ax[2], k = 0;
+  for (int d = 0; d < 3; ++d)
+    if (d != pe) ax[k++] = d;
+  int64_t n[3];
+  for (int d = 0; d < 3; ++d) n[d] = m[d] + (d == pe ? 1 : 0);
+  const int64_t cst[3] = {m[1] * m[2], m[2], 1};
+  const int64_t nst[3] = {n[1] * n[2], n[2], 1};
+  g.mp = (int32_t)m[pe];
+  g.nx = (int32_t)m[ax[0]];
+  g.ny = (int32_t)m[ax[1]];
+  g.pe = pe;
+  g.ncol = (int64_t)g.nx * g.ny;
+  g.cxs = cst[ax[0]];
+  g.cys = cst[ax[1]];
+  g.cps = cst[pe];
+  g.nxs = nst[ax[0]];
+  g.nys = nst[ax[1]];
+  g.nps = nst[pe];
+  g.ncell = m[0] * m[1] * m[2];
+  g.nnode = n[0] * n[1] * n[2];
+  g.hx = h[ax[0]];
+  g.hy = h[ax[1]];
+  g.hp = h[pe];
+  g.vol = h[0] * h[1] * h[2];
+  g.by_ny = make_fastdiv((uint32_t)g.ny);
+  g.by_nct = make_fastdiv((uint32_t)((g.ncol + kWave - 1) / kWave));
+  return g;
+}
+
 namespace {
 
 thread_local int g_last_hip = 0;
@@ -109,37 +140,6 @@ rgp_status check_grid(const rgp_grid* g) {
   if (g->m[2] + (g->pe == 2 ? 1 : 0) > 512) return RGP_ESHAPE;
   (void)cells;
   return RGP_OK;
-}
-
-Geom make_geom(const int64_t m[3], int pe, const double h[3]) {
-  Geom g{};
-  int ax[2], k = 0;
-  for (int d = 0; d < 3; ++d)
-    if (d != pe) ax[k++] = d;
-  int64_t n[3];
-  for (int d = 0; d < 3; ++d) n[d] = m[d] + (d == pe ? 1 : 0);
-  const int64_t cst[3] = {m[1] * m[2], m[2], 1};
-  const int64_t nst[3] = {n[1] * n[2], n[2], 1};
-  g.mp = (int32_t)m[pe];
-  g.nx = (int32_t)m[ax[0]];
-  g.ny = (int32_t)m[ax[1]];
-  g.pe = pe;
-  g.ncol = (int64_t)g.nx * g.ny;
-  g.cxs = cst[ax[0]];
-  g.cys = cst[ax[1]];
-  g.cps = cst[pe];
-  g.nxs = nst[ax[0]];
-  g.nys = nst[ax[1]];
-  g.nps = nst[pe];
-  g.ncell = m[0] * m[1] * m[2];
-  g.nnode = n[0] * n[1] * n[2];
-  g.hx = h[ax[0]];
-  g.hy = h[ax[1]];
-  g.hp = h[pe];
-  g.vol = h[0] * h[1] * h[2];
-  g.by_ny = make_fastdiv((uint32_t)g.ny);
-  g.by_nct = make_fastdiv((uint32_t)((g.ncol + kWave - 1) / kWave));
-  return g;
 }
 
 Geom geom_of(const rgp_grid* gr) { return make_geom(gr->m, gr->pe, gr->h); }

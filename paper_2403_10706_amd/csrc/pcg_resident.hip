@@ -51,7 +51,7 @@ typedef unsigned long long u64;
 
 constexpr int kResBlock = 512;
 constexpr u64 kArriveTicks = 2000000;    // 20 ms of the 100 MHz clock
-constexpr u64 kWaitTicks = 200000000;    // 2 s: only a lost workgroup could make a wait this long
+constexpr u64 kWaitTicks = 200000000;    // 2 s
 
 __device__ __forceinline__ void word_put(u64* p, u64 v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -82,10 +82,11 @@ __device__ __forceinline__ double value_of(const u64 (&u)[2]) {
 }
 
 // Waits for K values at indexes n[] of `w` (kNullOff: not wanted, gives 0); all loads of a round
-// are in flight together.  False when the wait was given up.
+// are in flight together.  False when the wait was given up after `spins` rounds.  (Rounds and not
+// time: none pass while the device runs something else.)
 template <typename TR, int K>
 __device__ __forceinline__ bool values_get(const u64* w, const uint32_t (&n)[K], uint32_t tag,
-                                           TR (&v)[K]) {
+                                           uint32_t spins, TR (&v)[K]) {
   constexpr int W = sizeof(TR) / 4;
   u64 u[K][W];
 #pragma unroll
@@ -99,12 +100,12 @@ __device__ __forceinline__ bool values_get(const u64* w, const uint32_t (&n)[K],
     for (int j = 0; j < W; ++j) ok &= (uint32_t)(u[k][j] >> 32) == tag;
     return ok || n[k] == kNullOff;
   };
-  u64 t0 = 0;
   for (uint32_t spin = 0;; ++spin) {
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < K; ++k) ok &= arrived(k);
     if (ok) break;
+    if (spin == spins) return false;
     // only what has not arrived is read again
     __builtin_amdgcn_s_sleep(1);
 #pragma unroll
@@ -113,11 +114,6 @@ __device__ __forceinline__ bool values_get(const u64* w, const uint32_t (&n)[K],
 #pragma unroll
         for (int j = 0; j < W; ++j) u[k][j] = word_get(word_at(w, 8u * (W * n[k] + j)));
       }
-    if ((spin & 63u) == 63u) {
-      const u64 now = wall_clock64();
-      if (t0 == 0) t0 = now;
-      if (now - t0 > kWaitTicks) return false;
-    }
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) v[k] = n[k] != kNullOff ? value_of(u[k]) : TR(0);
@@ -137,7 +133,8 @@ __device__ __forceinline__ double uniform(double v) {
 // Thread t takes word t % 16 of units t / 16, t / 16 + 32, ... (J of them), so that loads are
 // consecutive; returns the sum over its units of sum (t % 16) / 2, on even threads.
 template <int J>
-__device__ __forceinline__ bool sums_get(const u64* part, int units, uint32_t tag, double& s) {
+__device__ __forceinline__ bool sums_get(const u64* part, int units, uint32_t tag, uint32_t spins,
+                                         double& s) {
   uint32_t n[J];
   float f[J];
   const int t = threadIdx.x;
@@ -146,7 +143,7 @@ __device__ __forceinline__ bool sums_get(const u64* part, int units, uint32_t ta
     const int u = t / 16 + j * (kResBlock / 16);
     n[j] = u < units && (t & 15) < 14 ? (uint32_t)(u * kResSumStride + (t & 15)) : kNullOff;
   }
-  const bool ok = values_get<float, J>(part, n, tag, f);
+  const bool ok = values_get<float, J>(part, n, tag, spins, f);
   s = 0.0;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
@@ -584,7 +581,7 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
           n[2 * NPT + j] = ok ? (uint32_t)(un.o0 + (int)q) * (uint32_t)P + (uint32_t)f : kNullOff;
           to[j] = (int)q * S + (h < nb ? h : un.teff + h);
         }
-        lost = !values_get<TR, 2 * NPT + kRows>(words, n, tag, v) || lost;
+        lost = !values_get<TR, 2 * NPT + kRows>(words, n, tag, a.spins, v) || lost;
 #pragma unroll
         for (int j = 0; j < kRows; ++j)
           if (n[2 * NPT + j] != kNullOff) lds[to[j]] = v[2 * NPT + j];
@@ -655,9 +652,9 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     }
     if (!KD && !KR) now = fetch(NPT - 1, 0, false);   // the update's, under the wait
     double us;
-    const bool got = a.units <= 64 ? sums_get<2>(part, a.units, tag, us)
-                                   : (a.units <= 128 ? sums_get<4>(part, a.units, tag, us)
-                                                     : sums_get<8>(part, a.units, tag, us));
+    const bool got = a.units <= 64    ? sums_get<2>(part, a.units, tag, a.spins, us)
+                     : a.units <= 128 ? sums_get<4>(part, a.units, tag, a.spins, us)
+                                      : sums_get<8>(part, a.units, tag, a.spins, us);
     if (!got) flag = 1;
     __syncthreads();   // (the row sums of this unit are read)
     if ((t & 1) == 0) sh[t / 16][(t & 15) / 2] = us;
@@ -719,21 +716,25 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     }
     if (fin) break;
   }
-  if (lost || flag) {   // a workgroup vanished: report it, the level stops with b unchanged
-    if (t == 0) {
+  // A wait was given up: some workgroup stands still.  A level stops with b unchanged and a status; a
+  // plain solve shows it in all its outputs: x of this unit and the residual NaN, -1 iterations.
+  const bool failed = lost || flag;
+  if (failed && t == 0) {
+    if (gn) {
       __hip_atomic_store(&a.st->gn_stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (a.gn_mode && a.st->status == 0) a.st->status = RGP_EHIP;
-      if (a.relres_out) *a.relres_out = __longlong_as_double(0x7ff8000000000000LL);
+      if (a.st->status == 0) a.st->status = RGP_EHIP;
     }
-    return false;
+    if (a.iters_out) *a.iters_out = -1;
+    if (a.relres_out) *a.relres_out = __longlong_as_double(0x7ff8000000000000LL);
   }
 #pragma unroll
   for (int q = 0; q < XL; ++q)
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
       const TR xv = i < XN ? xlds[(i * XL + q) * kResBlock] : x[q][i >= XN ? i - XN : 0];
-      bst<TR>(rX, at(q < np && has(i, kOwn), node(q, i)), xv);
+      bst<TR>(rX, at(q < np && has(i, kOwn), node(q, i)), failed ? (TR)__builtin_nan("") : xv);
     }
+  if (failed) return false;
   if (ub == 0 && t == 0) {
     PcgSlot c{};
     c.iters = its;
@@ -834,6 +835,7 @@ ResArgs make_res_args(const Geom& g, const ResPlan& L, double alpha) {
   a.nnode = (uint32_t)g.nnode;
   a.ncell = (uint32_t)g.ncell;
   a.by_2nb = make_fastdiv((uint32_t)(2 * L.m.nb));
+  a.spins = kResSpins;
   a.cx = alpha * g.vol / (g.hx * g.hx);
   a.cy = alpha * g.vol / (g.hy * g.hy);
   return a;

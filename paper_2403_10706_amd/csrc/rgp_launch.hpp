@@ -196,6 +196,7 @@ constexpr int kMaxResVolumes = 12;       // volumes of one launch (their argumen
 constexpr size_t kMaxResLds = 156 * 1024;
 constexpr int kResSumStride = 16;        // words of one unit's seven sums: a line of its own
 constexpr int kResSumWords = 2 * kResSumStride * kMaxResUnits;
+constexpr uint32_t kResSpins = 1u << 24;   // rounds (1 us or more each) after which a wait is given up
 constexpr int kResSyncWords = kResSumWords + kMaxResUnits + 1;
 struct ResArgs {
   const void* diag;
@@ -214,6 +215,7 @@ struct ResArgs {
   LossFinalArgs lf;           // gn_mode: J, D, S, P of the current iterate
   int32_t gn_mode, maxit;
   uint32_t patience;          // added to the wait for arrivals: volumes before this one may be solved first
+  uint32_t spins;             // rounds after which a wait for a word is given up
   uint32_t tag;               // first tag of this launch (tag .. tag + maxit are its own)
   int32_t no, na, nb, role, P, T, XL, noc, units;
   uint32_t nnode, ncell;
@@ -225,6 +227,9 @@ struct ResBatch {
   ResArgs v[kMaxResVolumes];
 };
 static_assert(sizeof(ResBatch) <= 4096, "kernel arguments");
+// Geometry of one volume (extents m in cells, phase-encoding axis pe, spacings h).
+Geom make_geom(const int64_t m[3], int pe, const double h[3]);
+
 struct ResPlan {
   bool ok;      // the volume fits
   MarchGeo m;
