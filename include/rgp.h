@@ -250,6 +250,12 @@ rgp_status rgp_gn_hvp(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
  * The solves inside rgp_correct, the plans and the batches choose in the same way (a plan holds
  * both forms and chooses at each launch).
  *
+ * The one-launch form wants the chip: its workgroups (up to one per CU) run at the same time.  Where
+ * other work (another process, a kernel of another stream) keeps some of them out for 0.2 ms, those
+ * that run do the whole solve, with the same results, at a cost of about 4 times its time when half
+ * of them run (1.15 instead of 0.27 ms for 20 iterations at 144x168x111; one launch per iteration
+ * 0.53 ms).
+ *
  * The workgroups of the one-launch form wait for each other's values, 2^24 polls (more than 16 s of
  * running) at most.  When one gives up, *iters_dev is -1, *relres_dev NaN and x NaN where its
  * workgroup writes it; the call has returned RGP_OK by then. */

@@ -17,8 +17,11 @@
 //
 // Residency.  Every workgroup publishes its arrival; the volume's first workgroup waits for all
 // arrivals and then publishes the decision to go.  Past that point all workgroups are resident and
-// every wait ends.  If other work keeps them from becoming resident for kArriveTicks, it decides
-// against it: the others leave and the first one solves the volume alone from memory.
+// every wait ends.  If other work (another process, a kernel of another stream that holds CUs) keeps
+// some of them out for kArriveTicks, those that have arrived share the units and work from memory
+// (res_share), and whoever arrives later joins at the next iteration: no workgroup has to be
+// resident but the first.  All sums are formed unit by unit in the same order, so the results are
+// the same bits however many take part.
 //
 // What bounds it (rgp_pcg_solve with 20 iterations, us per iteration, stepped against resident):
 //   25x25x17 FP32 14.5 / 5.1   72x84x56 17.9 / 7.0   144x168x111 33.9 / 14.1   200x200x132 54 / 28
@@ -50,8 +53,10 @@ namespace {
 typedef unsigned long long u64;
 
 constexpr int kResBlock = 512;
-constexpr u64 kArriveTicks = 2000000;    // 20 ms of the 100 MHz clock
-constexpr u64 kWaitTicks = 200000000;    // 2 s
+// 0.2 ms of the 100 MHz clock: about what a solve takes when all workgroups run, and less than what
+// sharing it costs more than that
+constexpr u64 kArriveTicks = 20000;
+constexpr uint32_t kDecisionPolls = 1u << 28;   // (it comes, or the first workgroup never ran)
 
 __device__ __forceinline__ void word_put(u64* p, u64 v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -208,6 +213,9 @@ __device__ __forceinline__ void res_sums(double (&acc)[7], TR pk, TR w, TR r, TR
 struct ResShared {
   double sh[kResBlock / 16][8];
   int flag;
+  int rank;                         // res_wait's answer
+  int step, members;                // res_share: what the first workgroup published
+  int arrived[kResBlock / kWave];   // res_share: newcomers seen by each wavefront
 };
 
 // Sum k of the rows' partial sums, on lane 8 k of every wavefront: eight lanes per sum.
@@ -268,76 +276,288 @@ __device__ __forceinline__ void res_outputs(const ResArgs& a, const PcgSlot& c) 
   if (a.relres_out) *a.relres_out = c.relres;
 }
 
-// The whole solve by one workgroup, from memory (the decision against residency): vectors r and p
-// in the two spare arrays, w in the first word array, which is cleared again at the end.
+// How a solve goes on, as the first workgroup publishes it.
+enum ResHow : uint32_t { kHowResident = 1, kHowShared = 2, kHowOver = 3 };
+constexpr int kGoResident = -2, kLeave = -1;
+
+// (Thread 0 of a workgroup but the first.)  Waits for the decision: kGoResident, this workgroup's
+// rank among those that share the solve, or kLeave when the solve is over.
+__device__ __forceinline__ int res_wait(const ResArgs& a, int ub) {
+  for (uint32_t n = 0; n < kDecisionPolls; ++n) {
+    const u64 how = word_get(a.sync + kResHow);
+    if ((uint32_t)(how >> 32) == a.tag) {
+      if ((uint32_t)how == kHowResident) return kGoResident;
+      if ((uint32_t)how == kHowOver) return kLeave;
+      const uint32_t mine = (uint32_t)word_get(a.sync + ub);
+      if (mine >= kResMember) return (int)(mine - kResMember);
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return kLeave;
+}
+
+// A given-up wait, in the outputs: a level stops with b unchanged and a status; a plain solve gives
+// -1 iterations, a residual that is NaN, and (by the caller) NaN in x.
+__device__ __forceinline__ void res_failed(const ResArgs& a) {
+  if (a.gn_mode) {
+    __hip_atomic_store(&a.st->gn_stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.st->status == 0) a.st->status = RGP_EHIP;
+  }
+  if (a.iters_out) *a.iters_out = -1;
+  if (a.relres_out) *a.relres_out = __longlong_as_double(0x7ff8000000000000LL);
+}
+
+// (res_share; res_body has the same lines in place: called from there, with the addresses formed on
+// each iteration, 144x168x111 took 2.5 % longer.)  The sums of all units, added in a fixed order, on
+// every thread.  False (and `flag` set) when the wait for one was given up.
+__device__ __forceinline__ bool res_totals(const ResArgs& a, uint32_t tag, double (*sh)[8], int& flag,
+                                           double (&ts)[7]) {
+  const u64* part = a.part + (size_t)(tag & 1u) * (kResSumStride * kMaxResUnits);
+  const int t = threadIdx.x;
+  double us;
+  const bool got = a.units <= 64    ? sums_get<2>(part, a.units, tag, a.spins, us)
+                   : a.units <= 128 ? sums_get<4>(part, a.units, tag, a.spins, us)
+                                    : sums_get<8>(part, a.units, tag, a.spins, us);
+  if (!got) flag = 1;
+  __syncthreads();   // (the row sums of this unit are read)
+  if ((t & 1) == 0) sh[t / 16][(t & 15) / 2] = us;
+  __syncthreads();
+  if (flag) return false;
+  const double tot = res_row_sum(sh);
+#pragma unroll
+  for (int k = 0; k < 7; ++k) ts[k] = read_lane(tot, 8 * k);
+  return true;
+}
+__device__ __forceinline__ void res_put_sums(const ResArgs& a, int ub, uint32_t tag, double s) {
+  const int t = threadIdx.x;
+  if (t < 56 && (t & 7) == 0) {
+    u64* mine = a.part + (size_t)(tag & 1u) * (kResSumStride * kMaxResUnits) + ub * kResSumStride + t / 4;
+    word_put(mine, tagged(tag, (uint32_t)__double2loint(s)));
+    word_put(mine + 1, tagged(tag, (uint32_t)__double2hiint(s)));
+  }
+}
+
+// The solve by the workgroups that have arrived, `rank` being this one's place among them (the first
+// workgroup has 0): member r of k takes the units r, r + k, ...  The vectors are in memory: r and p in
+// the two spare arrays, w in the first word array (its nodes are cleared again at the end).  A step
+// is the start of the vectors (step 0) or an iteration.  The first workgroup opens each step: it
+// waits until every member has finished the one before, admits newcomers, and publishes the number
+// of members and the scalars that a newcomer lacks.  A member's stores are released before it says
+// that it has finished and acquired when the next step opens, so units may change hands; within a
+// step the exchange of the sums parts the reads of the old p from the stores of the new one.
+// 20 iterations at 144x168x111 FP32: 1.15 ms by 128 workgroups and 5.2 ms by 16 (resident 0.27, one
+// launch per iteration 0.53); 72x84x56: 0.52 and 1.1 ms (0.13, 0.36).  The code of the smallest
+// variants stays within their 128 registers with 2 planes (FP32) and 1 (FP64) at a time.
 template <typename TR>
-__device__ __forceinline__ void res_alone(const ResArgs& a, ResShared& m) {
-  double (*sh)[8] = m.sh;
-  const int role = a.role;
-  const int t = threadIdx.x, na = a.na, nb = a.nb, no = a.no, P = a.P;
-  const TR* __restrict__ dg = static_cast<const TR*>(a.diag);
-  const TR* __restrict__ of = static_cast<const TR*>(a.off);
-  const TR* __restrict__ rhs = static_cast<const TR*>(a.rhs);
-  TR* x = static_cast<TR*>(a.x);
-  TR* r = static_cast<TR*>(a.spare_r);
-  TR* p = static_cast<TR*>(a.spare_p);
-  TR* w = reinterpret_cast<TR*>(a.words);
+__device__ __forceinline__ void res_share(const ResArgs& a, int rank, ResShared& m) {
+  constexpr uint32_t kSz = sizeof(TR);
+  constexpr int kG = sizeof(TR) == 4 ? 2 : 1;   // planes whose loads are in flight together
+  const int t = threadIdx.x, role = a.role, na = a.na, nb = a.nb, no = a.no, P = a.P;
+  const uint32_t nbytes = a.nnode * kSz;
+  const BRes rD = bres(a.diag, nbytes), rO = bres(a.off, nbytes), rB = bres(a.rhs, nbytes);
+  const BRes rX = bres(a.x, nbytes), rR = bres(a.spare_r, nbytes), rP = bres(a.spare_p, nbytes);
+  const BRes rW = bres(a.words, nbytes);
+  const TR sg = (TR)a.rhs_sign;
   TR c_o, c_a, c_b;
   res_couplings<TR>(a, role, c_o, c_a, c_b);
-  const uint32_t n = a.nnode;
-  for (uint32_t i = t; i < n; i += kResBlock) {
-    const TR rv = (TR)a.rhs_sign * rhs[i];
-    r[i] = rv;
-    p[i] = fmad(TR(0), TR(0), rv * (TR(1) / dg[i]));
-    x[i] = TR(0);
-  }
-  __syncthreads();
+  auto at = [&](bool ok, uint32_t n) -> uint32_t { return ok ? n * kSz : kNullOff; };
+  // body(plane position, node in the unit's first plane) over this thread's positions of a unit, which
+  // are those of the resident form
+  auto positions = [&](const ResUnit& un, auto body) {
+    for (int j = t; j < un.teff; j += kResBlock) {
+      const int l = j + nb < un.teff ? j + nb : j + nb - un.teff;
+      const int f = un.f0 + l;
+      body(f, (uint32_t)un.o0 * (uint32_t)P + (uint32_t)f);
+    }
+  };
+  bool in = t == 0;   // (first workgroup: workgroup t is a member)
+  bool lost = false;
+  int k = 1, it = rank == 0 ? 0 : -1;
+  double bn = 0.0, rel = 0.0;
   PcgSlot cur{};
-  for (int it = 1; it <= a.maxit; ++it) {
-    double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (uint32_t k = t; k < n; k += kResBlock) {
-      const int o = (int)(k / (uint32_t)P), f = (int)(k - (uint32_t)o * (uint32_t)P);
-      const int ia = f / nb, ib = f - ia * nb;
-      const TR pk = p[k], d = dg[k];
-      const TR pom = o > 0 ? p[k - P] : TR(0), pop = o < no - 1 ? p[k + P] : TR(0);
-      const TR pam = ia > 0 ? p[k - nb] : TR(0), pap = ia < na - 1 ? p[k + nb] : TR(0);
-      const TR pbm = ib > 0 ? p[k - 1] : TR(0), pbp = ib < nb - 1 ? p[k + 1] : TR(0);
-      TR ol = TR(0);
-      if (role == 0 && o > 0) ol = of[k - P];
-      if (role == 1 && ia > 0) ol = of[k - nb];
-      if (role == 2 && ib > 0) ol = of[k - 1];
-      const TR wv = res_stencil<TR>(role, d, pk, pom, pop, pam, pap, pbm, pbp, ol, of[k], c_o, c_a,
-                                    c_b);
-      w[k] = wv;
-      const TR rd = TR(1) / d, rv = r[k];
-      res_sums<TR>(acc, pk, wv, rv, rv * rd, rd);
-    }
-    const double s = res_block_sum(acc, sh);
-    double ts[7];
-#pragma unroll
-    for (int k = 0; k < 7; ++k) ts[k] = read_lane(s, 8 * k);
-    __syncthreads();
-    bool fin = false;
-    cur = pcg_advance(cur, ts, it, a.maxit, a.rtol, fin);
-    if (cur.status == kPcgDone) break;
-    const TR al = (TR)cur.alpha, be = (TR)cur.beta;
-    for (uint32_t i = t; i < n; i += kResBlock) {
-      const TR pv = p[i];
-      if (fin) {
-        x[i] = x[i] + al * pv;
-      } else {
-        x[i] = fmad(al, pv, x[i]);
-        const TR rv = fmad(-al, w[i], r[i]);
-        r[i] = rv;
-        p[i] = fmad(be, pv, rv * (TR(1) / dg[i]));
+  while (true) {
+    bool late = false;
+    if (rank == 0) {
+      if (it > 0 && t > 0 && t < k) {
+        late = true;
+        for (uint32_t n = 0; n <= a.spins && late; ++n) {
+          late = (uint32_t)(word_get(a.sync + kResDone + t) >> 32) != a.tag + (uint32_t)it - 1u;
+          if (late) __builtin_amdgcn_s_sleep(1);
+        }
       }
+      const int room = min(a.units, a.most + it * a.grow), wv = t / kWave;
+      const bool want = t > 0 && t < a.units && !in && word_get(a.sync + t) == tagged(a.tag, 1u);
+      const u64 b = __ballot(want);
+      if ((t & (kWave - 1)) == 0) m.arrived[wv] = __popcll(b);
+      __syncthreads();
+      int r = k + __popcll(b & ((1ull << (t & (kWave - 1))) - 1ull)), all = k;
+      for (int j = 0; j < kResBlock / kWave; ++j) {
+        r += j < wv ? m.arrived[j] : 0;
+        all += m.arrived[j];
+      }
+      if (want && r < room) {
+        word_put(a.sync + t, tagged(a.tag, kResMember + (uint32_t)r));
+        in = true;
+      }
+      k = uniform(min(all, room));
+      if (t == 0) {
+        const uint32_t tag = a.tag + (uint32_t)it;
+        word_put(a.sync + kResScal + 0, tagged(tag, (uint32_t)__double2loint(bn)));
+        word_put(a.sync + kResScal + 1, tagged(tag, (uint32_t)__double2hiint(bn)));
+        word_put(a.sync + kResScal + 2, tagged(tag, (uint32_t)__double2loint(rel)));
+        word_put(a.sync + kResScal + 3, tagged(tag, (uint32_t)__double2hiint(rel)));
+        word_put(a.sync + kResStep, tagged(tag, (uint32_t)k));
+      }
+    } else {
+      if (t == 0) {
+        late = true;
+        for (uint32_t n = 0; n <= a.spins && late; ++n) {
+          const u64 v = word_get(a.sync + kResStep);
+          const uint32_t st = (uint32_t)(v >> 32) - a.tag;
+          late = it < 0 ? st > (uint32_t)a.maxit || (uint32_t)v <= (uint32_t)rank : st != (uint32_t)it;
+          m.step = (int)st;
+          m.members = (int)(uint32_t)v;
+          if (late) __builtin_amdgcn_s_sleep(1);
+        }
+      }
+      __syncthreads();
+      it = uniform(m.step);
+      k = uniform(m.members);
+    }
+    lost = __syncthreads_or(late);
+    if (lost) break;
+    if (rank > 0) {
+      const uint32_t n[2] = {0u, 1u};
+      double v[2];
+      late = !values_get<double, 2>(a.sync + kResScal, n, a.tag + (uint32_t)it, a.spins, v);
+      bn = v[0];
+      rel = v[1];
+      lost = __syncthreads_or(late);
+      if (lost) break;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (it == 0) {
+      for (int u = rank; u < a.units; u += k) {
+        const ResUnit un = res_unit(a, u);
+        positions(un, [&](int, uint32_t n0) {
+          for (int q = 0; q < un.np; ++q) {
+            const uint32_t o = (n0 + (uint32_t)q * (uint32_t)P) * kSz;
+            const TR rv = sg * bld<TR>(rB, o);
+            bst<TR>(rR, o, rv);
+            bst<TR>(rP, o, fmad(TR(0), TR(0), rv * (TR(1) / bld<TR>(rD, o))));
+            bst<TR>(rX, o, TR(0));
+          }
+        });
+      }
+    } else {
+      const uint32_t tag = a.tag + (uint32_t)it;
+      for (int u = rank; u < a.units; u += k) {   // w = H p and the unit's sums
+        const ResUnit un = res_unit(a, u);
+        double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+        positions(un, [&](int f, uint32_t n0) {
+          const int ia = f / nb, ib = f - ia * nb;
+          TR pom = bld<TR>(rP, at(un.o0 > 0, n0 - (uint32_t)P)), pk = bld<TR>(rP, n0 * kSz);
+          TR ol = role == 0 ? bld<TR>(rO, at(un.o0 > 0, n0 - (uint32_t)P)) : TR(0);
+          for (int q0 = 0; q0 < un.np; q0 += kG) {
+            TR pop[kG], pam[kG], pap[kG], pbm[kG], pbp[kG], d[kG], ou[kG], lo[kG], r[kG];
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+              const bool on = q0 + g < un.np;
+              const uint32_t n = n0 + (uint32_t)(q0 + g) * (uint32_t)P;
+              pop[g] = bld<TR>(rP, at(on && un.o0 + q0 + g < no - 1, n + (uint32_t)P));
+              pam[g] = bld<TR>(rP, at(on && ia > 0, n - (uint32_t)nb));
+              pap[g] = bld<TR>(rP, at(on && ia < na - 1, n + (uint32_t)nb));
+              pbm[g] = bld<TR>(rP, at(on && ib > 0, n - 1u));
+              pbp[g] = bld<TR>(rP, at(on && ib < nb - 1, n + 1u));
+              d[g] = bld<TR>(rD, at(on, n));
+              ou[g] = bld<TR>(rO, at(on, n));
+              lo[g] = bld<TR>(rO, at(on && ((role == 1 && ia > 0) || (role == 2 && ib > 0)),
+                                     n - (role == 1 ? (uint32_t)nb : 1u)));
+              r[g] = bld<TR>(rR, at(on, n));
+            }
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+              if (q0 + g >= un.np) break;
+              if (role != 0) ol = lo[g];
+              const TR wv = res_stencil<TR>(role, d[g], pk, pom, pop[g], pam[g], pap[g], pbm[g],
+                                            pbp[g], ol, ou[g], c_o, c_a, c_b);
+              bst<TR>(rW, (n0 + (uint32_t)(q0 + g) * (uint32_t)P) * kSz, wv);
+              const TR inv = TR(1) / d[g];
+              res_sums<TR>(acc, pk, wv, r[g], r[g] * inv, inv);
+              pom = pk;
+              pk = pop[g];
+              if (role == 0) ol = ou[g];
+            }
+          }
+        });
+        res_put_sums(a, u, tag, res_block_sum(acc, m.sh));
+        __syncthreads();   // m.sh is read
+      }
+      double ts[7];
+      if (!res_totals(a, tag, m.sh, m.flag, ts)) {
+        lost = true;
+        break;
+      }
+      PcgSlot prev{};
+      prev.bnorm2 = bn;
+      prev.relres = rel;
+      bool fin = false;
+      cur = pcg_advance(prev, ts, it, a.maxit, a.rtol, fin);
+      bn = cur.bnorm2;
+      rel = cur.relres;
+      if (cur.status == kPcgDone) break;   // keep x
+      const TR al = (TR)cur.alpha, be = (TR)cur.beta;
+      for (int u = rank; u < a.units; u += k) {
+        const ResUnit un = res_unit(a, u);
+        positions(un, [&](int, uint32_t n0) {
+          for (int q0 = 0; q0 < un.np; q0 += kG) {
+            TR x[kG], r[kG], p[kG], w[kG], d[kG];
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+              const uint32_t o = at(q0 + g < un.np, n0 + (uint32_t)(q0 + g) * (uint32_t)P);
+              x[g] = bld<TR>(rX, o);
+              r[g] = bld<TR>(rR, o);
+              p[g] = bld<TR>(rP, o);
+              w[g] = bld<TR>(rW, o);
+              d[g] = bld<TR>(rD, o);
+            }
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+              const uint32_t o = at(q0 + g < un.np, n0 + (uint32_t)(q0 + g) * (uint32_t)P);
+              const TR rv = fmad(-al, w[g], r[g]);
+              bst<TR>(rX, o, fin ? x[g] + al * p[g] : fmad(al, p[g], x[g]));
+              bst<TR>(rR, o, rv);
+              bst<TR>(rP, o, fmad(be, p[g], rv * (TR(1) / d[g])));
+            }
+          }
+        });
+      }
+      if (fin) break;
     }
     __syncthreads();
-    if (fin) break;
+    if (t == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (rank > 0) word_put(a.sync + kResDone + rank, tagged(a.tag + (uint32_t)it, 1u));
+    }
+    ++it;
   }
-  __syncthreads();
-  for (uint32_t i = t; i < n; i += kResBlock) w[i] = TR(0);
-  if (t == 0) res_outputs(a, cur);
+  for (int u = rank; u < a.units; u += k) {
+    const ResUnit un = res_unit(a, u);
+    positions(un, [&](int, uint32_t n0) {
+      for (int q = 0; q < un.np; ++q) {
+        const uint32_t o = (n0 + (uint32_t)q * (uint32_t)P) * kSz;
+        bst<TR>(rW, o, TR(0));
+        if (lost) bst<TR>(rX, o, (TR)__builtin_nan(""));
+      }
+    });
+  }
+  if (t == 0) {
+    if (lost)
+      res_failed(a);
+    else if (rank == 0)
+      res_outputs(a, cur);
+    if (rank == 0) word_put(a.sync + kResHow, tagged(a.tag, kHowOver));
+  }
 }
 
 // Makes v opaque to the compiler: values derived from it are not kept across iterations.
@@ -363,9 +583,10 @@ struct ResTier {
 // One unit's share of the solve (see the head of the file): at most NPT plane positions per thread
 // and XL planes.  A thread's position i is (t + i * kResBlock + nb) mod T, so that the rows next
 // to other units (the tile's first and last) belong to the last positions, which an update takes
-// and publishes first.  True when this (the volume's first) workgroup is to solve it alone.
+// and publishes first.  Returns this workgroup's rank among those that share the solve, where not
+// all could become resident; else negative.
 template <typename TR, int ROLE, int NPT, int XL, int KEEP, int XN, int S>
-__device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m) {
+__device__ __forceinline__ int res_body(const ResArgs& a, int ub, ResShared& m) {
   constexpr bool KD = (KEEP & kKeepDiag) != 0, KR = (KEEP & kKeepRecip) != 0,
                  KO = (KEEP & kKeepOff) != 0;
   constexpr uint32_t kSz = sizeof(TR);
@@ -448,13 +669,13 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     const bool stop = load_flag(&a.st->gn_stop) != 0;
     block_sum<5, kResBlock>(lsum);
     const bool viol = finalize_loss_sums(a.lf, lsum, !stop && ub == 0);
-    if (stop || viol) return false;   // the same in every workgroup
+    if (stop || viol) return kLeave;   // the same in every workgroup
   }
 
-  // residency: all arrived, or the first workgroup alone
+  // residency: all arrived, or those that have share the solve
   if (ub == 0) {
-    bool ok = true;
-    if (t < a.units) {
+    bool ok = a.most >= a.units;
+    if (ok && t < a.units) {
       const u64 t0 = wall_clock64();
       while ((uint32_t)(word_get(a.sync + t) >> 32) != tag0) {
         if (wall_clock64() - t0 > kArriveTicks + a.patience) {
@@ -463,29 +684,14 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
         }
       }
     }
-    __syncthreads();
-    if (!ok) flag = 1;
-    __syncthreads();
-    const bool alone = flag != 0;
-    if (t == 0) word_put(a.sync + kMaxResUnits, tagged(tag0, alone ? 2u : 1u));
-    if (alone) return true;
+    const bool share = __syncthreads_or(!ok);
+    if (t == 0) word_put(a.sync + kResHow, tagged(tag0, share ? kHowShared : kHowResident));
+    if (share) return 0;
   } else {
-    if (t == 0) {
-      u64 v = 0;
-      const u64 t0 = wall_clock64();
-      int go = 0;
-      while (true) {
-        v = word_get(a.sync + kMaxResUnits);
-        if ((uint32_t)(v >> 32) == tag0) {
-          go = (uint32_t)v == 1u;
-          break;
-        }
-        if (wall_clock64() - t0 > kWaitTicks) break;
-      }
-      flag = go ? 0 : 1;
-    }
+    if (t == 0) m.rank = res_wait(a, ub);
     __syncthreads();
-    if (flag) return false;
+    const int rank = uniform(m.rank);
+    if (rank != kGoResident) return rank;
   }
 
   TR c_o, c_a, c_b;
@@ -716,17 +922,8 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
     }
     if (fin) break;
   }
-  // A wait was given up: some workgroup stands still.  A level stops with b unchanged and a status; a
-  // plain solve shows it in all its outputs: x of this unit and the residual NaN, -1 iterations.
-  const bool failed = lost || flag;
-  if (failed && t == 0) {
-    if (gn) {
-      __hip_atomic_store(&a.st->gn_stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (a.st->status == 0) a.st->status = RGP_EHIP;
-    }
-    if (a.iters_out) *a.iters_out = -1;
-    if (a.relres_out) *a.relres_out = __longlong_as_double(0x7ff8000000000000LL);
-  }
+  const bool failed = lost || flag;   // some workgroup stands still
+  if (failed && t == 0) res_failed(a);
 #pragma unroll
   for (int q = 0; q < XL; ++q)
 #pragma unroll
@@ -734,14 +931,14 @@ __device__ __forceinline__ bool res_body(const ResArgs& a, int ub, ResShared& m)
       const TR xv = i < XN ? xlds[(i * XL + q) * kResBlock] : x[q][i >= XN ? i - XN : 0];
       bst<TR>(rX, at(q < np && has(i, kOwn), node(q, i)), failed ? (TR)__builtin_nan("") : xv);
     }
-  if (failed) return false;
+  if (failed) return kLeave;
   if (ub == 0 && t == 0) {
     PcgSlot c{};
     c.iters = its;
     c.relres = rel;
     res_outputs(a, c);
   }
-  return false;
+  return kLeave;
 }
 
 template <typename TR, int NPT, int XL, int KEEP, int XN, int S>
@@ -752,14 +949,14 @@ __global__ __launch_bounds__(kResBlock, XL <= 2 ? 4 : 2) void k_pcg_resident(Res
   const int ub = (int)blockIdx.x - b.start[p];
   if (ub >= a.units) return;
   __shared__ ResShared m;
-  bool alone;
+  int rank;
   if (a.role == 0)
-    alone = res_body<TR, 0, NPT, XL, KEEP, XN, S>(a, ub, m);
+    rank = res_body<TR, 0, NPT, XL, KEEP, XN, S>(a, ub, m);
   else if (a.role == 1)
-    alone = res_body<TR, 1, NPT, XL, KEEP, XN, S>(a, ub, m);
+    rank = res_body<TR, 1, NPT, XL, KEEP, XN, S>(a, ub, m);
   else
-    alone = res_body<TR, 2, NPT, XL, KEEP, XN, S>(a, ub, m);
-  if (alone) res_alone<TR>(a, m);
+    rank = res_body<TR, 2, NPT, XL, KEEP, XN, S>(a, ub, m);
+  if (rank >= 0) res_share<TR>(a, rank, m);
 }
 
 __global__ __launch_bounds__(kBlock) void k_clear_words(uint4* p, uint64_t n, u64* q, uint32_t nq) {
@@ -836,6 +1033,7 @@ ResArgs make_res_args(const Geom& g, const ResPlan& L, double alpha) {
   a.ncell = (uint32_t)g.ncell;
   a.by_2nb = make_fastdiv((uint32_t)(2 * L.m.nb));
   a.spins = kResSpins;
+  a.most = (int32_t)L.m.units;
   a.cx = alpha * g.vol / (g.hx * g.hx);
   a.cy = alpha * g.vol / (g.hy * g.hy);
   return a;

@@ -197,7 +197,13 @@ constexpr size_t kMaxResLds = 156 * 1024;
 constexpr int kResSumStride = 16;        // words of one unit's seven sums: a line of its own
 constexpr int kResSumWords = 2 * kResSumStride * kMaxResUnits;
 constexpr uint32_t kResSpins = 1u << 24;   // rounds (1 us or more each) after which a wait is given up
-constexpr int kResSyncWords = kResSumWords + kMaxResUnits + 1;
+// After the sums, words for the workgroups' standing: arrivals by workgroup (1, then kResMember + rank
+// of one that shares the solve); of those, by rank, the last step finished; how the solve goes on;
+// the open step with its number of members; two scalars of it.
+constexpr uint32_t kResMember = 16;
+constexpr int kResDone = kMaxResUnits, kResHow = 2 * kMaxResUnits, kResStep = kResHow + 1;
+constexpr int kResScal = kResStep + 1;
+constexpr int kResSyncWords = kResSumWords + kResScal + 4;
 struct ResArgs {
   const void* diag;
   const void* off;
@@ -205,8 +211,8 @@ struct ResArgs {
   void* x;
   unsigned long long* words;  // exchanged p: two parities of one word per 32 bits of the field
   unsigned long long* part;   // exchanged sums: two parities of [kMaxResUnits][kResSumStride]
-  unsigned long long* sync;   // arrivals [kMaxResUnits], then the decision
-  void* spare_r;              // two vectors outside `words` (the solve by one workgroup)
+  unsigned long long* sync;   // the workgroups' standing
+  void* spare_r;              // two vectors outside `words` (the shared solve)
   void* spare_p;
   double rhs_sign, cx, cy, rtol;
   State* st;
@@ -216,6 +222,8 @@ struct ResArgs {
   int32_t gn_mode, maxit;
   uint32_t patience;          // added to the wait for arrivals: volumes before this one may be solved first
   uint32_t spins;             // rounds after which a wait for a word is given up
+  int32_t most, grow;         // most workgroups that take part at first (fewer than units: in the
+                              // shared solve), and how many more each step
   uint32_t tag;               // first tag of this launch (tag .. tag + maxit are its own)
   int32_t no, na, nb, role, P, T, XL, noc, units;
   uint32_t nnode, ncell;

@@ -3,7 +3,10 @@
 // runs gave, for tests/test_gpu_resident_limits.py.  The limits are fields of the kernel's argument
 // block that the host sets; whatever they are, every workgroup ends by itself.
 //
-//   resident_driver n0 n1 n2 pe f32|f64 maxit rtol spins
+//   resident_driver n0 n1 n2 pe f32|f64 maxit rtol spins most grow cus
+//
+// spins, most, grow: the argument block's (most 0: every workgroup).  cus: the second run's stream has
+// the lowest `cus` of each 32 compute units only (0: all), so that not all workgroups are resident.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -31,6 +34,12 @@ struct Result {
   std::vector<unsigned char> x;
   int32_t iters;
   double relres;
+  float ms;
+};
+
+struct Limits {
+  uint32_t spins;
+  int most, grow, cus;
 };
 
 template <typename T>
@@ -42,7 +51,7 @@ int nans(const Result& r) {
 }
 
 template <typename T>
-int run(const int64_t m[3], int pe, DType real, int maxit, double rtol, uint32_t spins) {
+int run(const int64_t m[3], int pe, DType real, int maxit, double rtol, const Limits& lim) {
   const double h[3] = {1.0, 1.0, 1.0};
   const Geom g = make_geom(m, pe, h);
   const ResPlan R = plan_resident(g, real);
@@ -75,8 +84,16 @@ int run(const int64_t m[3], int pe, DType real, int maxit, double rtol, uint32_t
   for (int k = 0; k < 3; ++k)
     CHECK(hipMemcpy(vec + k * pad, host[k].data(), nb, hipMemcpyHostToDevice));
   CHECK(hipMemset(out, 0, so + 256));
-  hipStream_t s;
+  hipStream_t s, narrow = nullptr;
   CHECK(hipStreamCreate(&s));
+  if (lim.cus > 0) {
+    uint32_t mask[8];
+    for (uint32_t& w : mask) w = lim.cus >= 32 ? 0xffffffffu : (1u << lim.cus) - 1u;
+    CHECK(hipExtStreamCreateWithCUMask(&narrow, 8, mask));
+  }
+  hipEvent_t e0, e1;
+  CHECK(hipEventCreate(&e0));
+  CHECK(hipEventCreate(&e1));
   ResArgs a = make_res_args(g, R, 300.0);
   a.diag = vec;
   a.off = vec + pad;
@@ -98,10 +115,19 @@ int run(const int64_t m[3], int pe, DType real, int maxit, double rtol, uint32_t
   Result res[3];
   for (int k = 0; k < 3; ++k) {
     ResArgs b = a;
-    if (k == 1) b.spins = spins;
-    CHECK(hipMemsetAsync(a.x, 0x7f, nb, s));   // (no value of a solve)
-    CHECK(launch_pcg_resident_one(b, R, real, s));
-    CHECK(hipStreamSynchronize(s));
+    if (k == 1) {
+      b.spins = lim.spins;
+      if (lim.most > 0) b.most = lim.most;
+      b.grow = lim.grow;
+    }
+    const hipStream_t on = k == 1 && narrow ? narrow : s;
+    CHECK(hipMemset(a.x, 0x7f, nb));   // (no value of a solve)
+    CHECK(hipDeviceSynchronize());
+    CHECK(hipEventRecord(e0, on));
+    CHECK(launch_pcg_resident_one(b, R, real, on));
+    CHECK(hipEventRecord(e1, on));
+    CHECK(hipStreamSynchronize(on));
+    CHECK(hipEventElapsedTime(&res[k].ms, e0, e1));
     a.tag += (uint32_t)maxit + 1u;
     res[k].x.resize(nb);
     CHECK(hipMemcpy(res[k].x.data(), a.x, nb, hipMemcpyDeviceToHost));
@@ -111,9 +137,9 @@ int run(const int64_t m[3], int pe, DType real, int maxit, double rtol, uint32_t
   std::printf("{\"units\": %d, \"tier\": %d, \"role\": %d, \"nodes\": %lld, \"runs\": [", a.units,
               R.tier, a.role, (long long)g.nnode);
   for (int k = 0; k < 3; ++k)
-    std::printf("%s{\"equal\": %s, \"nans\": %d, \"iters\": %d, \"relres\": \"%.17g\"}", k ? ", " : "",
+    std::printf("%s{\"equal\": %s, \"nans\": %d, \"iters\": %d, \"relres\": \"%.17g\", \"ms\": %.3f}", k ? ", " : "",
                 res[k].x == res[0].x ? "true" : "false", nans<T>(res[k]), (int)res[k].iters,
-                res[k].relres);
+                res[k].relres, res[k].ms);
   std::printf("]}\n");
   return 0;
 }
@@ -121,15 +147,16 @@ int run(const int64_t m[3], int pe, DType real, int maxit, double rtol, uint32_t
 }  // namespace
 
 int main(int argc, char** argv) {
-  if (argc != 9) {
-    std::fprintf(stderr, "usage: resident_driver n0 n1 n2 pe f32|f64 maxit rtol spins\n");
+  if (argc != 12) {
+    std::fprintf(stderr, "usage: resident_driver n0 n1 n2 pe f32|f64 maxit rtol spins most grow cus\n");
     return 2;
   }
   const int64_t m[3] = {std::atoll(argv[1]), std::atoll(argv[2]), std::atoll(argv[3])};
   const int pe = std::atoi(argv[4]), maxit = std::atoi(argv[6]);
   const double rtol = std::atof(argv[7]);
-  const uint32_t spins = (uint32_t)std::strtoul(argv[8], nullptr, 10);
+  const Limits lim{(uint32_t)std::strtoul(argv[8], nullptr, 10), std::atoi(argv[9]),
+                   std::atoi(argv[10]), std::atoi(argv[11])};
   const bool f64 = std::strcmp(argv[5], "f64") == 0;
-  return f64 ? run<double>(m, pe, DType::F64, maxit, rtol, spins)
-             : run<float>(m, pe, DType::F32, maxit, rtol, spins);
+  return f64 ? run<double>(m, pe, DType::F64, maxit, rtol, lim)
+             : run<float>(m, pe, DType::F32, maxit, rtol, lim);
 }
