@@ -244,11 +244,13 @@ rgp_status rgp_gn_hvp(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
  *
  * Two forms of the same iteration.  A volume whose vectors fit the chip (about 5 M nodes in FP32,
  * 0.9 M in FP64, at most 256 nodes along the contiguous axis) is solved by one launch that keeps
- * them there; else, inside a caller's own stream capture, and while such a launch is still running
- * on another stream of the device, one launch per iteration.  Their block sums are added in
- * different orders, so results agree to rounding; each form by itself is bitwise reproducible.
- * The solves inside rgp_correct, the plans and the batches choose in the same way (a plan holds
- * both forms and chooses at each launch).
+ * them there; else, inside a caller's own stream capture, and on a stream or device with fewer than
+ * 256 CUs, one launch per iteration.  So the form depends on the call alone, and each form is bitwise
+ * reproducible whatever else runs; between them the block sums are added in different orders, and
+ * results agree to rounding.  Calls whose workgroups do not fit the chip beside those of calls that
+ * are unfinished on other streams are ordered behind them on the device.  The solves inside
+ * rgp_correct, the plans and the batches go by the same rules (a plan holds both forms; a captured
+ * rgp_plan_launch takes the second).
  *
  * The one-launch form wants the chip: its workgroups (up to one per CU) run at the same time.  Where
  * other work (another process, a kernel of another stream) keeps some of them out for 0.2 ms, those

@@ -292,72 +292,176 @@ rgp_status check_opts(const rgp_solver_opts* o) {
   return RGP_OK;
 }
 
-// Whether resident launches may be issued on a stream now, and the note that they were.  Two of
-// them running side by side on one device would each wait for CUs that the other holds, so they
-// are issued only where the ones issued last are on the same stream or have finished; a call that
-// finds them running elsewhere takes the stepped form, and so does one inside a caller's own
-// capture, whose replays are not seen here.  One event per device, made at its first use.
+// What a call's resident launches want at the same time: the most workgroups, and whether two of them
+// fit a CU.
+struct ResNeed {
+  int workgroups = 0;
+  bool paired = true;
+  void add(int n, int tier) {
+    workgroups = std::max(workgroups, n);
+    paired = paired && resident_paired(tier);
+  }
+};
+
+// The order of the resident launches of one device.  Those that may run at the same time are kept
+// within the chip: a call whose launches do not fit beside the ones unfinished on other streams waits
+// for one of them, on the device (hipStreamWaitEvent).  (Beside each other they would still end, but
+// share their solves, see res_share.)  Whether a call is resident (mine) depends on the call alone:
+// not inside a caller's own capture, whose replays are not seen here, nor on a stream that lacks some
+// of the device's CUs.
+//
+// Counted per XCD, to which workgroups are dealt round-robin: one to a CU, two where all calls are of
+// the kind that pairs.  What runs at one time are calls of which none waited for another, and the one
+// issued last counted all the others.  One event per entry, made at its first use and recorded
+// behind each call's launches; the device's mutex is held while they are issued.
+//
+// Plans replayed on 1, 2, 4 and 8 streams, us a correction (5 steps a level): 32x32x24 FP64 353, 201,
+// 119, 113 (three run beside each other); 72x84x56 FP32 with 20 iterations 1352, 819, 828, 849 (two);
+// 144x168x111 2938, 3033, 3056, 3063 (one after the other; in one launch per iteration 5150, 3759,
+// 3369, 3208).
 class ResidentTurn {
  public:
-  explicit ResidentTurn(hipStream_t s) : s_(s) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return;
+  ResidentTurn(hipStream_t s, const ResNeed& need) : s_(s) {
     int dev = 0;
     hipDevice_t on = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return;
-    if (s && (hipStreamGetDevice(s, &on) != hipSuccess || (int)on != dev)) return;
-    // another thread may be capturing in a mode that forbids event calls everywhere
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
-    {
-      std::lock_guard<std::mutex> lk(mu());
-      Device& d = devices()[dev];
-      if (d.cus < 0 &&
-          (hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-           hipEventCreateWithFlags(&d.last, hipEventDisableTiming) != hipSuccess))
-        d.cus = 0;
-      bool free = d.cus >= kMaxResUnits && !d.issuing;
-      if (free && d.any && d.stream != s) {
-        free = hipEventQuery(d.last) == hipSuccess;
-        if (!free) (void)hipGetLastError();
-      }
-      if (free) {
-        d.issuing = true;
-        d_ = &d;
-      }
-    }
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!ok(hipStreamIsCapturing(s, &cs)) || cs != hipStreamCaptureStatusNone ||
+        !ok(hipGetDevice(&dev)) || dev < 0 || dev >= kDevices ||
+        (s && (!ok(hipStreamGetDevice(s, &on)) || (int)on != dev)) || !whole_device(s) ||
+        // another thread may be capturing in a mode that forbids event calls everywhere
+        !ok(hipThreadExchangeStreamCaptureMode(&mode)))
+      return;
+    static Device devices[kDevices];
+    Device& d = devices[dev];
+    lock_ = std::unique_lock<std::mutex>(d.mu);
+    if (!order(d, dev, std::min((need.workgroups + kXcds - 1) / kXcds, kXcdCus), need.paired))
+      lock_.unlock();
+    (void)ok(hipThreadExchangeStreamCaptureMode(&mode));
   }
   ~ResidentTurn() {
-    if (!d_) return;
-    std::lock_guard<std::mutex> lk(mu());
-    (void)hipEventRecord(d_->last, s_);
-    d_->stream = s_;
-    d_->any = true;
-    d_->issuing = false;
+    if (!mine()) return;
+    mine_->live = ok(hipEventRecord(mine_->done, s_)) || mine_->live;
+    mine_->stream = s_;
   }
   ResidentTurn(const ResidentTurn&) = delete;
   ResidentTurn& operator=(const ResidentTurn&) = delete;
-  bool mine() const { return d_ != nullptr; }
+  bool mine() const { return mine_ != nullptr; }
 
  private:
-  static constexpr int kDevices = 64;
-  struct Device {
-    int cus = -1;
-    hipEvent_t last = nullptr;
+  static constexpr int kDevices = 64, kXcds = 8, kXcdCus = kMaxResUnits / kXcds, kEntries = 32;
+  struct Entry {
+    hipEvent_t done = nullptr;
     hipStream_t stream = nullptr;
-    bool any = false, issuing = false;
+    int cus = 0;          // of an XCD
+    bool paired = false;
+    bool live = false;    // unfinished when last asked
+    uint64_t age = 0;     // order of issue
+    uint32_t after = 0;   // entries (as they were then) that this one's call follows
   };
-  static std::mutex& mu() {
-    static std::mutex m;
+  struct Device {
+    std::mutex mu;
+    int cus = -1;
+    uint64_t issued = 0;
+    Entry e[kEntries];
+  };
+
+  static bool ok(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+  }
+  static bool whole_device(hipStream_t s) {
+    uint32_t mask[kMaxResUnits / 16] = {};
+    if (!ok(hipExtStreamGetCUMask(s, sizeof(mask) / sizeof(mask[0]), mask))) return false;
+    int n = 0;
+    for (uint32_t w : mask) n += __builtin_popcount(w);
+    return n >= kMaxResUnits;
+  }
+  // Entries that whoever waits for entry i follows.
+  static uint32_t behind(const Device& d, int i) {
+    uint32_t m = 1u << i;
+    for (int j = 0; j < kEntries; ++j)
+      if ((d.e[i].after >> j & 1u) && d.e[j].age < d.e[i].age) m |= 1u << j;
     return m;
   }
-  static Device* devices() {
-    static Device d[kDevices];
-    return d;
+  // Whether the live entries but those in `gone` leave room for `cus` more: they are parted into
+  // chains, oldest first, of entries of which each follows the one before, so that at most one of a
+  // chain runs at a time.
+  static bool room(const Device& d, uint32_t gone, int cus, bool paired) {
+    int tail[kEntries], most[kEntries], chains = 0;
+    uint32_t left = 0;
+    for (int j = 0; j < kEntries; ++j)
+      if (d.e[j].live && !(gone >> j & 1u)) left |= 1u << j;
+    while (left) {
+      const int j = oldest(d, left);
+      left &= ~(1u << j);
+      const uint32_t m = behind(d, j);
+      int c = 0;
+      while (c < chains && !(m >> tail[c] & 1u)) ++c;
+      if (c == chains) most[chains++] = 0;
+      tail[c] = j;
+      most[c] = std::max(most[c], d.e[j].cus);
+      paired = paired && d.e[j].paired;
+    }
+    for (int c = 0; c < chains; ++c) cus += most[c];
+    return cus <= (paired ? 2 * kXcdCus : kXcdCus);
   }
+  static int oldest(const Device& d, uint32_t of) {
+    int o = -1;
+    for (int j = 0; j < kEntries; ++j)
+      if ((of >> j & 1u) && (o < 0 || d.e[j].age < d.e[o].age)) o = j;
+    return o;
+  }
+  bool order(Device& d, int dev, int cus, bool paired) {
+    if (d.cus < 0 &&
+        !ok(hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev)))
+      return false;
+    if (d.cus < kMaxResUnits) return false;
+    int own = -1, idle = -1;
+    uint32_t live = 0, gone = 0;   // gone: what this call follows
+    for (int j = 0; j < kEntries; ++j) {
+      Entry& e = d.e[j];
+      if (e.live && ok(hipEventQuery(e.done))) e.live = false;
+      if (e.live) live |= 1u << j;
+      if (e.live && e.stream == s_) own = j;
+      if (!e.live && idle < 0) idle = j;
+    }
+    auto follow = [&](int j) -> bool {
+      gone |= behind(d, j);
+      return ok(hipStreamWaitEvent(s_, d.e[j].done, 0));
+    };
+    // an equal handle may stand for another stream by now (of another thread, or made after the
+    // first was destroyed): its work is waited for as well, which costs its own stream nothing
+    if (own >= 0 && !follow(own)) return false;
+    // the oldest entry behind which there is room, or the newest and again
+    while (!room(d, gone, cus, paired)) {
+      int j = -1;
+      for (uint32_t left = live & ~gone; left; left &= ~(1u << j)) {
+        j = oldest(d, left);
+        if (room(d, gone | behind(d, j), cus, paired)) break;
+      }
+      if (j < 0 || !follow(j)) return false;
+    }
+    // an entry for this call: its stream's, an idle one, or the oldest, which it then follows
+    int at = own >= 0 ? own : idle;
+    if (at < 0) {
+      at = oldest(d, live);
+      if (!(gone >> at & 1u) && !follow(at)) return false;
+    }
+    Entry& e = d.e[at];
+    if (!e.done && !ok(hipEventCreateWithFlags(&e.done, hipEventDisableTiming))) return false;
+    // (until then the entry stands for what it did)
+    e.cus = e.live ? std::max(e.cus, cus) : cus;
+    e.paired = paired && (e.paired || !e.live);
+    e.age = ++d.issued;
+    e.after = gone;
+    mine_ = &e;
+    return true;
+  }
+
   hipStream_t s_;
-  Device* d_ = nullptr;
+  std::unique_lock<std::mutex> lock_;
+  Entry* mine_ = nullptr;
 };
 
 // The Armijo passes of one step on the direction in w.X: gamma = 1 alone (it is accepted in most
@@ -1074,7 +1178,9 @@ rgp_status rgp_pcg_solve(const rgp_grid* grid, rgp_dtype real_t, const void* hdi
   for (int i = 0; i < 6; ++i) vec[i] = c.take(g.nnode * dsize(dr));
   const ResPlan R = plan_resident(g, dr);
   if (R.ok) {
-    const ResidentTurn turn(s);
+    ResNeed need;
+    need.add((int)R.m.units, R.tier);
+    const ResidentTurn turn(s, need);
     if (turn.mine()) {
       ResArgs ra = make_res_args(g, R, alpha);
       ra.diag = hdiag;
@@ -1381,19 +1487,21 @@ hipError_t release(CapturedGraph& g) {
 }  // namespace
 
 // A plan holds the sequence in both forms of the PCG (resident only where a level fits it); each
-// launch takes the one that the device's other work allows (ResidentTurn).
+// launch takes the one that is due there (ResidentTurn).
 struct rgp_plan_s {
   CapturedGraph resident, stepped;
+  ResNeed need;
 };
 
 namespace {
 
-// Captures what `issue(resident)` enqueues on s, once or in both forms, into a new plan.
+// Captures what `issue(resident)` enqueues on s into a new plan, in both forms where the resident one
+// has workgroups.
 template <typename F>
-rgp_status make_plan(hipStream_t s, bool resident, rgp_plan* plan, F issue) {
+rgp_status make_plan(hipStream_t s, const ResNeed& need, rgp_plan* plan, F issue) {
   CapturedGraph g[2];
   rgp_status st = RGP_OK;
-  for (int f = 0; f < (resident ? 2 : 1) && st == RGP_OK; ++f) {
+  for (int f = 0; f < (need.workgroups ? 2 : 1) && st == RGP_OK; ++f) {
     hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
       st = issue(f == 1);
@@ -1406,7 +1514,7 @@ rgp_status make_plan(hipStream_t s, bool resident, rgp_plan* plan, F issue) {
       if (st == RGP_OK) st = RGP_EHIP;
     }
   }
-  rgp_plan p = st == RGP_OK ? new (std::nothrow) rgp_plan_s{g[1], g[0]} : nullptr;
+  rgp_plan p = st == RGP_OK ? new (std::nothrow) rgp_plan_s{g[1], g[0], need} : nullptr;
   if (!p) {
     (void)release(g[0]);
     (void)release(g[1]);
@@ -1416,7 +1524,9 @@ rgp_status make_plan(hipStream_t s, bool resident, rgp_plan* plan, F issue) {
   return RGP_OK;
 }
 
-uint32_t grid_resident_levels(const rgp_grid* grid, const rgp_solver_opts* o, rgp_dtype real_t) {
+// Levels of a correction that are solved in the resident form, and what they need.
+uint32_t grid_resident_levels(const rgp_grid* grid, const rgp_solver_opts* o, rgp_dtype real_t,
+                              ResNeed* need = nullptr) {
   DType dr;
   Level lv[kMaxLevels];
   if (o->solver != RGP_SOLVER_GN || o->gn_iters < 1 || !dtype_of(real_t, &dr) ||
@@ -1424,7 +1534,13 @@ uint32_t grid_resident_levels(const rgp_grid* grid, const rgp_solver_opts* o, rg
     return 0;
   // every resident launch of a solve has its own tags
   if ((int64_t)o->levels * o->gn_iters * (o->pcg_iters + 1) >= (int64_t(1) << 31)) return 0;
-  return resident_levels(lv, o->levels, dr);
+  const uint32_t m = resident_levels(lv, o->levels, dr);
+  for (int l = 0; need && l < o->levels; ++l)
+    if (m >> l & 1u) {
+      const ResPlan R = plan_resident(lv[l].g, dr);
+      need->add((int)R.m.units, R.tier);
+    }
+  return m;
 }
 
 }  // namespace
@@ -1439,9 +1555,10 @@ rgp_status rgp_correct(const rgp_grid* grid, rgp_dtype img_t, const void* I_plus
                                 ws_bytes);
   if (st != RGP_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  const uint32_t resident = grid_resident_levels(grid, opts, real_t);
+  ResNeed need;
+  const uint32_t resident = grid_resident_levels(grid, opts, real_t, &need);
   if (resident) {
-    const ResidentTurn turn(s);
+    const ResidentTurn turn(s, need);
     if (turn.mine())
       return enqueue_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, T_plus,
                              T_minus, stats_dev, ws, resident, s);
@@ -1462,10 +1579,11 @@ rgp_status rgp_correct_plan(const rgp_grid* grid, rgp_dtype img_t, const void* I
                                 ws_bytes);
   if (st != RGP_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  return make_plan(s, grid_resident_levels(grid, opts, real_t) != 0, plan, [&](bool resident) {
+  ResNeed need;
+  const uint32_t levels = grid_resident_levels(grid, opts, real_t, &need);
+  return make_plan(s, need, plan, [&](bool resident) {
     return enqueue_correct(grid, img_t, I_plus, I_minus, real_t, opts, b_init, b_out, T_plus,
-                           T_minus, stats_dev, ws,
-                           resident ? grid_resident_levels(grid, opts, real_t) : 0u, s);
+                           T_minus, stats_dev, ws, resident ? levels : 0u, s);
   });
 }
 
@@ -1473,7 +1591,7 @@ rgp_status rgp_plan_launch(rgp_plan plan, void* stream) {
   if (!plan) return RGP_EINVAL;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   if (plan->resident.exec) {
-    const ResidentTurn turn(s);
+    const ResidentTurn turn(s, plan->need);
     if (turn.mine()) {
       RGP_HIP(hipGraphLaunch(plan->resident.exec, s));
       return RGP_OK;
@@ -1657,6 +1775,7 @@ struct BatchSequence {
   std::vector<BatchSlot> slots;
   std::vector<unsigned char> arena;
   unsigned char* arena_dev = nullptr;
+  ResNeed need;   // of the resident launches
 };
 
 // Levels whose PCG solves are single entries of the pairs' sequences: those that some pair runs in
@@ -1756,6 +1875,8 @@ rgp_status record_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
     }
     if (r0.kind == RecKind::kPcgSolve) {
       pack_solves(recs, i, sl.solves);
+      for (const ResidentLaunch& l : sl.solves)
+        seq.need.add(l.b.start[l.b.n], l.tier);
       continue;
     }
     if (r0.kind == RecKind::kOther || n == 1 || !same) continue;
@@ -1927,7 +2048,7 @@ rgp_status rgp_correct_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
                                 T_minus, stats_dev, ws, ws_bytes, s, seq);
   if (st != RGP_OK) return st;
   if (!seq[1].slots.empty()) {
-    const ResidentTurn turn(s);
+    const ResidentTurn turn(s, seq[1].need);
     if (turn.mine()) {
       RGP_HIP(issue_batch(n, seq[1], s));
       return RGP_OK;
@@ -1951,7 +2072,7 @@ rgp_status rgp_correct_batch_plan(int32_t n, const rgp_grid* grids, rgp_dtype im
   rgp_status st = prepare_batch(n, grids, img_t, I_plus, I_minus, real_t, opts, b_out, T_plus,
                                 T_minus, stats_dev, ws, ws_bytes, s, seq);
   if (st != RGP_OK) return st;
-  return make_plan(s, !seq[1].slots.empty(), plan, [&](bool resident) {
+  return make_plan(s, seq[1].need, plan, [&](bool resident) {
     const hipError_t e = issue_batch(n, seq[resident ? 1 : 0], s);
     if (e == hipSuccess) return RGP_OK;
     g_last_hip = (int)e;

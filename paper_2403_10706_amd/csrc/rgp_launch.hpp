@@ -495,6 +495,8 @@ hipError_t launch_pcg_step_plan(const PcgArgs& a, DType real, const PcgPlan& L, 
 hipError_t launch_pcg_scalars(const PcgScalarArgs& a, hipStream_t s);
 constexpr size_t dsize_real(DType t) { return t == DType::F64 ? 8 : 4; }
 ResPlan plan_resident(const Geom& g, DType real);
+// Whether two workgroups of a variant fit a CU (at most 128 registers and half of the LDS).
+constexpr bool resident_paired(int tier) { return tier == 0; }
 ResArgs make_res_args(const Geom& g, const ResPlan& L, double alpha);
 // Clears the exchange words of a volume of nnode nodes and the sums and arrivals at `sync`
 // (kResSyncWords words) before the first resident launch of a solve.
