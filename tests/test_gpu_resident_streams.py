@@ -18,6 +18,11 @@ def _workspace(rgp, shape, pe, dt):
                        dtype=torch.uint8, device=DEV)
 
 
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    return ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+
+
 class _Handle:
     """A stream known by its handle."""
 
@@ -51,7 +56,8 @@ def test_overlapping_solves_are_bitwise_equal(shape, pe, dt, streams):
 
 
 def test_threads_on_their_own_default_streams():
-    """hipStreamPerThread is one handle for a stream of each thread."""
+    """hipStreamPerThread is one handle for a stream of each thread (which ends with its thread: each
+    waits for its own work)."""
     from paper_2403_10706_amd import rgp
     shape, pe = (97, 113, 75), 1
     d, o, r = _system(rgp, shape, pe, F32)
@@ -59,13 +65,14 @@ def test_threads_on_their_own_default_streams():
     ws = [_workspace(rgp, shape, pe, F32) for _ in range(4)]
     xs = [[torch.full_like(r, 7.0) for _ in range(4)] for _ in ws]
     torch.cuda.synchronize()
-    errors = []
+    errors, hip = [], _hip()
 
     def work(w, x):
         try:
             torch.cuda.set_device(0)
             for y in x:
                 rgp.pcg_solve_into(d, o, r, y, shape, pe, 40, w, stream=_Handle(2))
+            assert hip.hipStreamSynchronize(ctypes.c_void_p(2)) == 0
         except Exception as e:   # noqa: BLE001
             errors.append(e)
 
@@ -74,7 +81,6 @@ def test_threads_on_their_own_default_streams():
         t.start()
     for t in threads:
         t.join(60)
-    torch.cuda.synchronize()
     assert not errors, errors
     for x in xs:
         for y in x:
@@ -112,8 +118,7 @@ def test_overlapping_plans_are_bitwise_equal():
 
 def test_stream_without_all_compute_units_is_stepped():
     from paper_2403_10706_amd import rgp
-    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
-    hip = ctypes.CDLL(hip)
+    hip = _hip()
     handle = ctypes.c_void_p()
     mask = (ctypes.c_uint32 * 8)(*[0xffff] * 8)
     assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
