@@ -249,8 +249,8 @@ rgp_status rgp_gn_hvp(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
  * reproducible whatever else runs; between them the block sums are added in different orders, and
  * results agree to rounding.  Calls whose workgroups do not fit the chip beside those of calls that
  * are unfinished on other streams are ordered behind them on the device.  The solves inside
- * rgp_correct, the plans and the batches go by the same rules (a plan holds both forms; a captured
- * rgp_plan_launch takes the second).
+ * rgp_correct, the plans and the batches go by the same rules (a plan holds both forms, for the
+ * streams it may be replayed on).
  *
  * The one-launch form wants the chip: its workgroups (up to one per CU) run at the same time.  Where
  * other work (another process, a kernel of another stream) keeps some of them out for 0.2 ms, those
