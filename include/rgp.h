@@ -336,9 +336,10 @@ rgp_status rgp_plan_destroy(rgp_plan plan);
  * buffers corrected by one captured HIP graph (replayed with rgp_plan_launch) in which every
  * Gauss-Newton kernel - loss_grad, the PCG scalar phase and steps, the Armijo passes and
  * decisions, the step update - is ONE launch covering all pairs, each pair's workgroups reading
- * their arguments from a table in the workspace (PCG solves in the one-launch form of
- * rgp_pcg_solve: as few launches as hold the pairs; not where batch_march is set); the pyramid, OT, prolongation and correction
- * kernels run pair by pair inside the same graph.  Per pair the arithmetic is that of
+ * their arguments from a table in the workspace; PCG solves in the one-launch form of rgp_pcg_solve
+ * take as few launches as hold the pairs, and pairs too large for it issue theirs one pair after the
+ * other beside those (with batch_march set, every pair shares one launch per iteration).  The
+ * pyramid, OT, prolongation and correction kernels run pair by pair inside the same graph.  Per pair the arithmetic is that of
  * rgp_correct (same options for all pairs; use_b_init must be 0; at most 1024 pairs; the
  * contiguous field axis of every pair at most 256 nodes, else RGP_ESHAPE).  I_plus, I_minus,
  * b_out: host arrays of n device pointers; T_plus, T_minus, stats_dev: NULL or host arrays of n
@@ -367,7 +368,8 @@ rgp_status rgp_correct_batch(int32_t n, const rgp_grid* grids, rgp_dtype img_t,
                              void* const* T_plus, void* const* T_minus, double* const* stats_dev,
                              void* ws, size_t ws_bytes, void* stream);
 
-/* Autotuner of the PCG tile shape (batching extension): for every pyramid level of `grid` under
+/* Autotuner of the tile shape of the PCG's form with one launch per iteration (batching extension;
+ * solves in one launch, see rgp_pcg_solve, do not use it): for every pyramid level of `grid` under
  * `opts` (one level when opts is NULL) it times the candidate march lengths of the PCG step - a
  * work unit is 256 consecutive positions of the contiguous node plane times XL planes - on the
  * workspace's own vectors (a correction workspace; their contents are overwritten, the parts the

@@ -69,15 +69,6 @@ struct Geom {
   FastDiv by_nct;   // column-kernel tile -> (run along PE, chunk of 64 columns)
 };
 
-__host__ __device__ inline int64_t cell_base(const Geom& g, int64_t col) {
-  const int64_t ix = col / g.ny, iy = col - (col / g.ny) * g.ny;
-  return ix * g.cxs + iy * g.cys;
-}
-__host__ __device__ inline int64_t node_base(const Geom& g, int64_t col) {
-  const int64_t ix = col / g.ny, iy = col - (col / g.ny) * g.ny;
-  return ix * g.nxs + iy * g.nys;
-}
-
 // Per-pair device scalars of the solver (written by one designated block of a kernel and read by
 // later kernels only, so kernel boundaries order every access).
 struct State {
