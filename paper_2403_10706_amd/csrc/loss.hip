@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_step_batch(const ApplyArgs* __
 // Corrected images T[I+, b, v] and T[I-, b, -v] at the cell centres (Sec. 2.4.7).  One wavefront has
 // 64 columns times a run of S cells: the field of the run, then all image taps in flight together,
 // through buffer descriptors (a tap outside the column reads 0, a store that is not wanted is
-// dropped).  Bound by memory: 140x140x92 FP32 moves 36 MB, 5.2 us at the rate of a large copy;
+// dropped).  Bound by memory: 140x140x92 FP32 moves 36 MB, 7.1 us at the rate of a large copy;
 // 11.3 us with 64-bit index divisions and a branch per tap, 8.0 us now (in a graph).
 template <typename TI>
 __device__ __forceinline__ void bst_img(BRes r, uint32_t off, TI v);

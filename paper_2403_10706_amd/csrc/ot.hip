@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kBlock) void k_shift(ShiftArgs a) {
   bool any = false;
   // kU elements of each image per thread and round, all loads in flight together (indices
   // clamped into the array; the surplus ones are not counted).  At 200x200x132 FP32 (42 MB): 15.2 us
-  // on 256 workgroups, 11.3 us on 512; the OT kernel, whose every block combines the extrema, 1.4 us
+  // on 256 workgroups, 12.2 us on 512; the OT kernel, whose every block combines the extrema, 1.4 us
   // more.
   constexpr int kU = 16;
   const int64_t stride = (int64_t)gridDim.x * kBlock;

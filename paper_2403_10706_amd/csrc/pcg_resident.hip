@@ -23,15 +23,20 @@
 // resident but the first.  All sums are formed unit by unit in the same order, so the results are
 // the same bits however many take part.
 //
-// What bounds it (rgp_pcg_solve with 20 iterations, us per iteration, stepped against resident):
-//   25x25x17 FP32 14.5 / 5.1   72x84x56 17.9 / 7.0   144x168x111 33.9 / 14.1   200x200x132 54 / 28
-//   32x32x24 FP64 19 / 5.5     90x90x90 FP64 31 / 12.2
-// Small volumes: two exchanges per iteration (outer p and sums), about 1 us of latency each, and
-// the workgroup barriers between.  144x168x111: of 12.7 us, 3.3 wait for the outer p (8 MB of words
-// each way), 2 for the sums, 2.3 + 1.6 are the stencil and its reduction (FP64 issue), 2.8 the update.
-// Above that d and the couplings no longer fit the registers and are read again from the L2, a group
-// of planes ahead of their use (200x200x132: stencil 8 and update 7 of 25 us; with a position's
-// planes read together, right before their use, 9.6 and 12 of 35).
+// What bounds it.  rgp_pcg_solve with 20 iterations, us per iteration, in one launch per iteration
+// (a graph of them) and in this form, whose fixed costs are about 12 us of the 20 iterations:
+//   25x25x17 FP32 6.6 / 5.0   72x84x56 11.2 / 6.5   144x168x111 27.5 / 13.3   200x200x132 48 / 24-25
+//   32x32x24 FP64 7.4 / 4.4   90x90x90 FP64 22.2 / 10.6
+// One workgroup's phases, us per iteration (read with wall_clock64 in a copy, which adds 0.1 to 1):
+//                wait for outer p   stencil   its sums   wait for all sums   update   sum
+//   25x25x17            1.4           0.5       0.4            1.0             1.0     4.3
+//   72x84x56            2.1           0.5       0.5            2.0             1.0     6.0
+//   144x168x111         4.0           2.2       1.6            2.1             2.5    12.4
+//   200x200x132         4.9           6.1       3.4            2.3             6.1    22.7
+// Small volumes: the two exchanges, about 1 us of latency each at least.  144x168x111: the outer p (8 MB
+// of words each way), then FP64 issue.  Above that d and the couplings no longer fit the registers and
+// are read again from the L2, a group of planes ahead of their use (with a position's planes read
+// together, right before their use, the stencil took 9.6 and the update 12).
 //
 // Arithmetic: node for node that of the stepped form (pcg.hip), with the block sums formed over
 // this form's own partition.
