@@ -269,7 +269,7 @@ def ot_init(I_plus: torch.Tensor, I_minus: torch.Tensor, pe: int, h=(1.0, 1.0, 1
     """Column-wise 1D OT initial field (see rgp_ot_init).  Returns (b0, n_guarded device tensor)."""
     _dev_check(I_plus, I_minus)
     real_dtype = real_dtype or (torch.float64 if I_plus.dtype == torch.float64 else torch.float32)
-    shape = tuple(I_plus.shape)
+    shape = I_plus.shape
     if out is None:
         out = torch.empty(field_shape(shape, pe), dtype=real_dtype, device=I_plus.device)
     ng = torch.zeros(1, dtype=torch.int64, device=I_plus.device)
@@ -300,7 +300,7 @@ def loss_grad(I_plus, I_minus, b, pe, h=(1.0, 1.0, 1.0), alpha=300.0, beta=1e-4,
               want_grad=True, want_hess=True, ws=None, stream=None):
     """Objective (device tensor [J, D, S, P] in FP64), gradient and banded GN Hessian."""
     _dev_check(I_plus, I_minus, b)
-    shape = tuple(I_plus.shape)
+    shape = I_plus.shape
     if tuple(b.shape) != field_shape(shape, pe):
         raise ValueError(f"field shape {tuple(b.shape)} != {field_shape(shape, pe)}")
     dev = b.device
@@ -323,7 +323,7 @@ def loss_grad_noalloc(I_plus, I_minus, b, pe, h=(1.0, 1.0, 1.0), alpha=300.0, be
     nothing is allocated here when every wanted output is given.  Returns (jdsp, grad, hdiag,
     hoff) as passed."""
     _dev_check(I_plus, I_minus, b)
-    shape = tuple(I_plus.shape)
+    shape = I_plus.shape
     if tuple(b.shape) != field_shape(shape, pe):
         raise ValueError(f"field shape {tuple(b.shape)} != {field_shape(shape, pe)}")
     g = _grid(shape, pe, h)
@@ -419,7 +419,7 @@ def correct_lsq(I_plus, I_minus, b, pe, h=(1.0, 1.0, 1.0), *, maxit=30, rtol=1e-
     """Least-squares corrected image (rgp_correct_lsq) in the images' dtype, and the CGLS
     iterations per column (int32 device tensor of the two cross-axis extents) or None."""
     _dev_check(I_plus, I_minus, b)
-    shape = tuple(I_plus.shape)
+    shape = I_plus.shape
     out = torch.empty_like(I_plus)
     cross = tuple(n for d, n in enumerate(shape) if d != pe)
     it = torch.empty(cross, dtype=torch.int32, device=b.device) if want_iters else None
@@ -493,7 +493,7 @@ def correct(I_plus, I_minus, pe, h=(1.0, 1.0, 1.0), opts: Optional[Options] = No
     _dev_check(I_plus, I_minus, b_init)
     opts = opts or Options()
     real_dtype = real_dtype or (torch.float64 if I_plus.dtype == torch.float64 else torch.float32)
-    shape = tuple(I_plus.shape)
+    shape = I_plus.shape
     dev = I_plus.device
     copts = opts.to_c(use_b_init=b_init is not None)
     b = out if out is not None else torch.empty(field_shape(shape, pe), dtype=real_dtype, device=dev)
