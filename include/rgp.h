@@ -248,7 +248,8 @@ rgp_status rgp_gn_hvp(const rgp_grid* grid, rgp_dtype real_t, const void* hdiag,
  * 256 CUs, one launch per iteration.  So the form depends on the call alone, and each form is bitwise
  * reproducible whatever else runs; between them the block sums are added in different orders, and
  * results agree to rounding.  Calls whose workgroups do not fit the chip beside those of calls that
- * are unfinished on other streams are ordered behind them on the device.  The solves inside
+ * are unfinished on other streams are ordered behind them on the device (so a program must not make
+ * an enqueued call wait for one that it enqueues later on another stream).  The solves inside
  * rgp_correct, the plans and the batches go by the same rules (a plan holds both forms, for the
  * streams it may be replayed on).
  *
